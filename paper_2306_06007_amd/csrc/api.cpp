@@ -41,8 +41,8 @@ hipError_t launch_interp(const PairDev *, const int64_t *, int, int64_t, const d
                          const void *, int64_t, double *, int64_t, int, int, double, double, int, hipStream_t);
 template <typename T>
 hipError_t launch_direct(const DirectItem *, int64_t, const double *, int64_t, const double *, int64_t,
-                         const int32_t *, const void *, int64_t, double *, int64_t, int, double, int, int64_t,
-                         const void *, hipStream_t);
+                         const int32_t *, const void *, int64_t, double *, int64_t, int, double, int, int, int,
+                         int64_t, const void *, hipStream_t);
 template <typename T>
 hipError_t launch_finalize(const double *, int64_t, const int32_t *, void *, int, hipStream_t);
 template <typename T>
@@ -322,7 +322,8 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
                 HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, dst, [&] {
                     return launch_direct<T>(dd.direct + i0, i1 - i0, sxyz, n_src, txyz, n_tgt, sperm,
                                             static_cast<const C *>(in) + static_cast<int64_t>(t0) * n_src, n_src,
-                                            sc.acc, 2 * n_tgt, nb, iota, det, direct_cap, pl->cis_tab, dst);
+                                            sc.acc, 2 * n_tgt, nb, iota, det, hp.wide_phase, real_only, direct_cap,
+                                            pl->cis_tab, dst);
                 }));
             }
             HVOX_TRY(hipEventRecord(pl->join_ev, pl->side));
@@ -379,7 +380,7 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
             HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, st, [&] {
                 return launch_direct<T>(dd.direct + i0, i1 - i0, sxyz, n_src, txyz, n_tgt, sperm,
                                         static_cast<const C *>(in) + static_cast<int64_t>(t0) * n_src, n_src, sc.acc,
-                                        2 * n_tgt, nb, iota, det, 0, pl->cis_tab, st);
+                                        2 * n_tgt, nb, iota, det, hp.wide_phase, real_only, 0, pl->cis_tab, st);
             }));
         }
         for (int r = 0; r < nb; ++r) {

@@ -38,6 +38,9 @@ constexpr int kDirectSrcTile = 256;  // sources staged in LDS at a time
 constexpr int kDirectSeg = 8192;     // longest source segment of a direct-sum work item
 constexpr int64_t kDirectMinItems = 4096;   // shorter segments while a plan has fewer direct work items
 constexpr int kDirectWgPerCu = 8;    // direct-sum workgroups per CU while NUFFT work runs beside it
+// float32 direct sum: phases of at most this many turns take their fraction from the
+// low word of a float64 sum (kernels.hip, kPhaseMagic); larger ones through a float64 fraction
+constexpr double kMaxMagicTurns = 262144.0;
 constexpr int kCisTab = 1024;        // entries exp(2 pi i k / kCisTab) of the float64 direct sum's phase table
 constexpr int kRowBatch = 4;         // data rows (ntrans) per direct-sum launch, most per NUFFT pass, accumulator rows
 constexpr int kInterpLanes = 16;     // interp: lanes per target
@@ -227,6 +230,7 @@ struct HostPlan {
     int rows = 1;
     int64_t ws_row = 0;
     int64_t max_pts = 0;                 // spread points of the largest batch
+    int wide_phase = 0;                  // 1: some phase may exceed kMaxMagicTurns
     // unique FFT-length tables: (n1, n2) pre-correction tables and n2 twiddles
     std::vector<double> precor_nu;       // nu = l / n2 of every pre-correction entry
     std::vector<int32_t> tw_len;         // lengths with a twiddle table

@@ -794,31 +794,26 @@ __device__ __forceinline__ void cis_rev(double t, double &c, double &s)
     c = (k == 1 || k == 2) ? -c1 : c1;
 }
 
-// exp(2 pi i t) in float64 from a table of exp(2 pi i k / kCisTab) (float64,
-// filled on the host) and the Taylor terms of the remainder: with u =
-// kCisTab t, k = rint(u) and f = u - k in [-1/2, 1/2], exp(2 pi i t) =
-// tab[k mod kCisTab] exp(i theta), theta = 2 pi f / kCisTab, |theta| <= pi /
-// kCisTab; sin theta ~ theta - theta^3 / 6 and cos theta ~ 1 - theta^2 / 2 +
-// theta^4 / 24 leave a truncation below theta^5 / 120 = 2.3e-15 (kCisTab =
-// 1024), the scale 2 pi / kCisTab folded into the coefficients.  k comes from
-// one add of 1.5 2^52, which rounds u to an integer in round-to-nearest and
-// leaves k + 2^51 in the low bits of the sum's mantissa (|u| < 2^51, i.e.
-// |t| < 2^41 turns); the scaling by a power of two and the split u = k + f
-// are exact.
-__device__ __forceinline__ void cis_tab(double t, const double2 *tab, double &c, double &s)
+// exp(2 pi i t) in float64, t given in table steps (u = kCisTab t), from a
+// table of exp(2 pi i k / kCisTab) (float64, filled on the host) and the Taylor
+// terms of the remainder: with k = rint(u) and f = u - k in [-1/2, 1/2],
+// exp(2 pi i t) = tab[k mod kCisTab] exp(i theta), theta = 2 pi f / kCisTab,
+// |theta| <= pi / kCisTab; sin theta ~ theta - theta^3 / 6 and cos theta ~ 1 -
+// theta^2 / 2 + theta^4 / 24 leave a truncation below theta^5 / 120 = 2.3e-15
+// (kCisTab = 1024), the scale 2 pi / kCisTab folded into the coefficients.  k
+// comes from one add of 1.5 2^52, which rounds u to an integer in
+// round-to-nearest and leaves k + 2^51 in the low bits of the sum's mantissa
+// (|u| < 2^51); the split u = k + f is exact.  Copies of a smaller table
+// interleaved so that no two lanes meet on an LDS bank (256 entries, 16 copies,
+// 64 KB, one more polynomial term) measured no faster with one data row and up
+// to 18% slower with four (fewer wavefronts): bank conflicts do not bound the loop.
+__device__ __forceinline__ void cis_tab(double u, const double2 *tab, double &c, double &s)
 {
     static_assert((kCisTab & (kCisTab - 1)) == 0, "power-of-two table");
     constexpr double kRound = 6755399441055744.0;                 // 1.5 * 2^52
     constexpr double a1 = 6.283185307179586476925287 / kCisTab;   // theta = a1 f
     constexpr double a3 = -a1 * a1 * a1 / 6.0, b2 = -a1 * a1 / 2.0, b4 = a1 * a1 * a1 * a1 / 24.0;
-    double u, m;
-    {
-        // separate multiply and add (no contraction): a fused form would need the
-        // 1.5 2^52 addend in a vector register per term
-#pragma clang fp contract(off)
-        u = t * static_cast<double>(kCisTab);
-        m = u + kRound;
-    }
+    const double m = u + kRound;
     const double f = u - (m - kRound);                             // [-1/2, 1/2]
     const double2 e = tab[__double2loint(m) & (kCisTab - 1)];       // k + 2^51 = k mod kCisTab
     const double f2 = f * f;
@@ -826,6 +821,20 @@ __device__ __forceinline__ void cis_tab(double t, const double2 *tab, double &c,
     const double cs = fma(f2, fma(f2, b4, b2), 1.0);
     c = fma(e.x, cs, -e.y * sn);
     s = fma(e.y, cs, e.x * sn);
+}
+
+// exp(2 pi i <a, b>) in float64: the products split exactly into a rounded
+// part, reduced to a fraction of a turn, and its rounding error
+__device__ __forceinline__ void cis_dot(const double a[3], const double b[3], double &c, double &s)
+{
+    double f = 0.0, e = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double p = a[d] * b[d];
+        e += fma(a[d], b[d], -p);
+        f += p - rint(p);
+    }
+    cis_rev(f + e, c, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -969,24 +978,133 @@ __global__ __launch_bounds__(256) void k_interp(const PairDev *__restrict__ pair
 // eps = 0 mode of Sect. 4):  f_k += sum_n c_n exp(2 pi i iota s_k.x_n).
 // A workgroup of 256 threads owns <= 512 targets (two per thread) and
 // <= kDirectSeg sources, staged 256 at a time in LDS, for NT data rows at
-// once (the phase factors are computed once and applied to every row).  Per source tile with reference
-// point x_S and target-tile reference s_T,
-//   s_k.x_n = s_k.x_S + s_T.(x_n - x_S) + (s_k - s_T).(x_n - x_S):
-// the first two terms are evaluated once per (target, tile) and
-// (source, tile); only the small third term is evaluated per (target,
-// source) pair.  Every phase is reduced to a fraction of a turn in float64
-// and its sine / cosine taken in the plan's precision for the per-pair term
-// (cis_rev), in float64 for the per-tile reference terms.  The sign iota
-// multiplies the target offsets and the reference phases, so the inner loop
-// always accumulates c exp(+2 pi i t).  Phases are float64 (full rate on CDNA).
+// once (the phase factors are computed once and applied to every row).  Phases
+// are float64 dot products (full rate on CDNA).  Float32 plans take them of the
+// coordinates themselves: a phase of |t| turns is rounded to |t| 2^-53.  Float64
+// plans take them relative to the first source x_S of the staged tile and rotate
+// the tile's sums by exp(2 pi i s_k.x_S), evaluated with exact products.  The
+// sign iota multiplies the target coordinates, so the inner loop always
+// accumulates c exp(+2 pi i t).
+//
+// What bounds it: VALU issue.  Per term the float32 loop issues three float64
+// FMAs (phase), one funnel shift (reduction to a fraction of a turn), sine and
+// cosine (two issue cycles each) and the multiply-adds: four, two when every
+// value of the staged tile is real (a real sky) or only the real part of the
+// result is wanted -- 12 or 10 lane-cycles.  Matrix instructions for the
+// multiply-adds (v_mfma_f32_4x4x1) do not overlap with the vector work and
+// measured 15.1 lane-cycles a term against 12.0.  The float64 loop issues 21.25
+// instructions (19.25 with real values) but takes 25.5 (23.0) lane-cycles of the
+// 2.4 GHz peak clock; without its table reads it measured 21.2 for 18
+// instructions, so the rest is not LDS (a clock held down by float64 power
+// fits).  247,500 x 250,000, 10^12 term-rows/s, real / complex values, before
+// (references per target and source tile, fraction and conversion, one path for
+// both kinds of values) and now:
+//   float32, 1 row 3.00 -> 3.92 / 3.34, 4 rows 7.16 -> 10.2 / 7.20;
+//   float64, 1 row 1.50 -> 1.71 / 1.54, 4 rows 3.64 -> 4.84 / 3.72.
 // ---------------------------------------------------------------------------
 
-template <typename T, int NT>
+// multiply-adds of a term: complex, real values only, real part of the result only
+enum DirectMode { kDirectComplex, kDirectRealIn, kDirectRealOut };
+
+// Float32 phase t + kPhaseMagic, accumulated as such by the FMAs: the sum of
+// 1.5 2^20 keeps every |t| < 2^19 turns (the planner's kMaxMagicTurns bounds them
+// with room) in one binade whose last bit is 2^-32 turns, so the
+// low word of the double is the fraction of a turn in 32 bits.  Its upper 23
+// bits become the mantissa of a float in [1, 2), which the hardware sine and
+// cosine take in revolutions: one funnel shift instead of a float64 fraction
+// and a conversion.  The added 2^-24 centres the truncation to 23 bits (an
+// error of at most 2^-24 turns).
+constexpr double kPhaseMagic = 1572864.0 + 0x1p-24;
+
+// exp(2 pi i t) of the phase q.x for one (target, source): float32 plans
+template <bool WIDE>
+__device__ __forceinline__ void direct_cis(const double q[3], double x, double y, double z, const double2 *, float &c,
+                                           float &s)
+{
+    float r;
+    if constexpr (WIDE) {   // phases beyond the magic range: float64 fraction
+        r = static_cast<float>(__builtin_amdgcn_fract(fma(q[0], x, fma(q[1], y, q[2] * z))));
+    } else {
+        const double m = fma(q[0], x, fma(q[1], y, fma(q[2], z, kPhaseMagic)));
+        r = __int_as_float(__builtin_amdgcn_alignbit(0x7f, __double2loint(m), 9));   // 1.fraction
+    }
+    s = __builtin_amdgcn_sinf(r);
+    c = __builtin_amdgcn_cosf(r);
+}
+// float64 plans: the LDS phase table (q holds the target in table steps)
+template <bool WIDE>
+__device__ __forceinline__ void direct_cis(const double q[3], double x, double y, double z, const double2 *tab,
+                                           double &c, double &s)
+{
+    cis_tab(fma(q[0], x, fma(q[1], y, q[2] * z)), tab, c, s);
+}
+
+// sources [jb, je) of the staged tile (a multiple of four) into the float64
+// sums of the thread's two targets; partial sums of kRun terms in the plan's
+// precision (64 in float32: the rounding of the running sum grows with its
+// length, and a run of 64 instead of 256 costs 0.06 instructions a term)
+template <typename T, int NT, bool WIDE, int MODE>
+__device__ __forceinline__ void direct_tile(int jb, int je, const double q0[3], const double q1[3], const double *lx,
+                                            const double *ly, const double *lz,
+                                            const cplx<T> (*lc)[kDirectSrcTile], const double2 *ltab,
+                                            double a0r[NT], double a0i[NT], double a1r[NT], double a1i[NT])
+{
+    constexpr int kRun = sizeof(T) == 4 ? 64 : kDirectSrcTile;
+    for (int j0 = jb; j0 < je; j0 += kRun) {
+        const int j1 = min(j0 + kRun, je);
+        T b0r[NT], b0i[NT], b1r[NT], b1i[NT];
+#pragma unroll
+        for (int r = 0; r < NT; ++r) {   // float64: straight into the caller's sums
+            b0r[r] = sizeof(T) == 4 ? T(0) : T(a0r[r]);
+            b0i[r] = sizeof(T) == 4 ? T(0) : T(a0i[r]);
+            b1r[r] = sizeof(T) == 4 ? T(0) : T(a1r[r]);
+            b1i[r] = sizeof(T) == 4 ? T(0) : T(a1i[r]);
+        }
+        for (int j = j0; j < j1; j += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double x = lx[j + u], y = ly[j + u], z = lz[j + u];
+                T c0, s0, c1, s1;
+                direct_cis<WIDE>(q0, x, y, z, ltab, c0, s0);
+                direct_cis<WIDE>(q1, x, y, z, ltab, c1, s1);
+                // one phase factor per (target, source), applied to every row
+#pragma unroll
+                for (int r = 0; r < NT; ++r) {
+                    const cplx<T> c = lc[r][j + u];
+                    if constexpr (MODE == kDirectRealIn) {
+                        b0r[r] = fma(c.x, c0, b0r[r]);
+                        b0i[r] = fma(c.x, s0, b0i[r]);
+                        b1r[r] = fma(c.x, c1, b1r[r]);
+                        b1i[r] = fma(c.x, s1, b1i[r]);
+                    } else {
+                        b0r[r] = fma(c.x, c0, fma(-c.y, s0, b0r[r]));
+                        b1r[r] = fma(c.x, c1, fma(-c.y, s1, b1r[r]));
+                        if constexpr (MODE == kDirectComplex) {
+                            b0i[r] = fma(c.x, s0, fma(c.y, c0, b0i[r]));
+                            b1i[r] = fma(c.x, s1, fma(c.y, c1, b1i[r]));
+                        }
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < NT; ++r) {
+            a0r[r] = sizeof(T) == 4 ? a0r[r] + (double)b0r[r] : (double)b0r[r];
+            a1r[r] = sizeof(T) == 4 ? a1r[r] + (double)b1r[r] : (double)b1r[r];
+            if constexpr (MODE != kDirectRealOut) {
+                a0i[r] = sizeof(T) == 4 ? a0i[r] + (double)b0i[r] : (double)b0i[r];
+                a1i[r] = sizeof(T) == 4 ? a1i[r] + (double)b1i[r] : (double)b1i[r];
+            }
+        }
+    }
+}
+
+template <typename T, int NT, bool WIDE>
 __device__ __forceinline__ void direct_item(const DirectItem it, const double *__restrict__ sxyz, int64_t nsrc,
                                             const double *__restrict__ txyz, int64_t ntgt,
                                             const int32_t *__restrict__ perm, const cplx<T> *__restrict__ in,
                                             int64_t in_stride, double *__restrict__ acc, int64_t acc_stride,
-                                            double iota, int det, double *lx, double *ly, double *lz,
+                                            double iota, int det, int real_out, double *lx, double *ly, double *lz,
                                             cplx<T> (*lc)[kDirectSrcTile], const double2 *ltab)
 {
     const int tid = threadIdx.x;
@@ -994,85 +1112,69 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
     const bool has0 = tid < it.tgt_cnt, has1 = tid + kDirectThreads < it.tgt_cnt;
     const int64_t k0 = it.tgt_off + (has0 ? tid : 0);
     const int64_t k1 = it.tgt_off + (has1 ? tid + kDirectThreads : 0);
-    double sT[3], sk0[3], sk1[3], sp0[3], sp1[3];
+    constexpr bool kRef = sizeof(T) == 8;   // phases relative to the staged tile's first source
+    const double unit = kRef ? iota * kCisTab : iota;   // the sign enters through the phase
+    double q0[3], q1[3];
     for (int d = 0; d < 3; ++d) {
-        sT[d] = txyz[d * ntgt + it.tgt_off];
-        sk0[d] = txyz[d * ntgt + k0];
-        sk1[d] = txyz[d * ntgt + k1];
-        sp0[d] = iota * (sk0[d] - sT[d]);        // the sign enters through the phase
-        sp1[d] = iota * (sk1[d] - sT[d]);
+        q0[d] = unit * txyz[d * ntgt + k0];
+        q1[d] = unit * txyz[d * ntgt + k1];
     }
     double a0r[NT], a0i[NT], a1r[NT], a1i[NT];
 #pragma unroll
     for (int r = 0; r < NT; ++r) a0r[r] = a0i[r] = a1r[r] = a1i[r] = 0.0;
     for (int s0 = 0; s0 < it.src_cnt; s0 += kDirectSrcTile) {
-        const int64_t nS = it.src_off + s0;
-        double xS[3];
-        for (int d = 0; d < 3; ++d) xS[d] = sxyz[d * nsrc + nS];
         const int cnt = min(kDirectSrcTile, it.src_cnt - s0);
+        const int64_t nS = it.src_off + s0;
+        double ref[3] = {0.0, 0.0, 0.0};
+        if constexpr (kRef)
+            for (int d = 0; d < 3; ++d) ref[d] = sxyz[d * nsrc + nS];
         __syncthreads();
-        if (tid < cnt) {
-            const int64_t n = nS + tid;
-            double dxv[3];
-            double ph = 0.0;
-            for (int d = 0; d < 3; ++d) {
-                dxv[d] = sxyz[d * nsrc + n] - xS[d];
-                ph += sT[d] * dxv[d];
-            }
-            lx[tid] = dxv[0];
-            ly[tid] = dxv[1];
-            lz[tid] = dxv[2];
-            double ec, es;
-            cis_rev(iota * ph, ec, es);   // exp(2 pi i iota ph), float64
+        bool im = false;   // a staged value has an imaginary part (NaN included)
+        {
+            // entries beyond the last source hold zeros: the loop runs in fours
+            const bool live = tid < cnt;
+            const int64_t n = nS + (live ? tid : 0);
+            lx[tid] = live ? sxyz[n] - ref[0] : 0.0;
+            ly[tid] = live ? sxyz[nsrc + n] - ref[1] : 0.0;
+            lz[tid] = live ? sxyz[2 * nsrc + n] - ref[2] : 0.0;
             const int64_t u = perm ? perm[n] : n;
 #pragma unroll
             for (int r = 0; r < NT; ++r) {
-                const cplx<T> c = in[r * in_stride + u];
-                lc[r][tid] = mk<T>(T(c.x * ec - c.y * es), T(c.x * es + c.y * ec));
+                const cplx<T> c = live ? in[r * in_stride + u] : mk<T>(T(0), T(0));
+                lc[r][tid] = c;
+                im |= !(c.y == T(0));
             }
         }
-        __syncthreads();
-        T b0r[NT], b0i[NT], b1r[NT], b1i[NT];
+        const bool cplx_in = __syncthreads_or(im);
+        const int je = (cnt + 3) & ~3;
+        if constexpr (!kRef) {
+            if (real_out)
+                direct_tile<T, NT, WIDE, kDirectRealOut>(0, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
+            else if (cplx_in)
+                direct_tile<T, NT, WIDE, kDirectComplex>(0, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
+            else direct_tile<T, NT, WIDE, kDirectRealIn>(0, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
+        } else {
+            double b0r[NT], b0i[NT], b1r[NT], b1i[NT];
 #pragma unroll
-        for (int r = 0; r < NT; ++r) b0r[r] = b0i[r] = b1r[r] = b1i[r] = T(0);
-#pragma unroll 4
-        for (int j = 0; j < cnt; ++j) {
-            const double xj = lx[j], yj = ly[j], zj = lz[j];
-            const double t0 = fma(sp0[0], xj, fma(sp0[1], yj, sp0[2] * zj));
-            const double t1 = fma(sp1[0], xj, fma(sp1[1], yj, sp1[2] * zj));
-            T c0, s0v, c1, s1v;
-            if constexpr (sizeof(T) == 8) {   // float64 plan: the LDS phase table
-                cis_tab(t0, ltab, c0, s0v);
-                cis_tab(t1, ltab, c1, s1v);
-            } else {                          // float32 plan: the hardware sine / cosine
-                cis_rev(t0, c0, s0v);
-                cis_rev(t1, c1, s1v);
+            for (int r = 0; r < NT; ++r) b0r[r] = b0i[r] = b1r[r] = b1i[r] = 0.0;
+            if (cplx_in)
+                direct_tile<T, NT, WIDE, kDirectComplex>(0, je, q0, q1, lx, ly, lz, lc, ltab, b0r, b0i, b1r, b1i);
+            else direct_tile<T, NT, WIDE, kDirectRealIn>(0, je, q0, q1, lx, ly, lz, lc, ltab, b0r, b0i, b1r, b1i);
+            // tile reference phases (q / kCisTab is exact)
+            double p0[3], p1[3], e0c, e0s, e1c, e1s;
+            for (int d = 0; d < 3; ++d) {
+                p0[d] = q0[d] * (1.0 / kCisTab);
+                p1[d] = q1[d] * (1.0 / kCisTab);
             }
-            // one phase factor per (target, source), applied to every row
+            cis_dot(p0, ref, e0c, e0s);
+            cis_dot(p1, ref, e1c, e1s);
 #pragma unroll
             for (int r = 0; r < NT; ++r) {
-                const cplx<T> c = lc[r][j];
-                b0r[r] = fma(c.x, c0, fma(-c.y, s0v, b0r[r]));
-                b0i[r] = fma(c.x, s0v, fma(c.y, c0, b0i[r]));
-                b1r[r] = fma(c.x, c1, fma(-c.y, s1v, b1r[r]));
-                b1i[r] = fma(c.x, s1v, fma(c.y, c1, b1i[r]));
+                a0r[r] += b0r[r] * e0c - b0i[r] * e0s;
+                a0i[r] += b0r[r] * e0s + b0i[r] * e0c;
+                a1r[r] += b1r[r] * e1c - b1i[r] * e1s;
+                a1i[r] += b1r[r] * e1s + b1i[r] * e1c;
             }
-        }
-        double ph0 = 0.0, ph1 = 0.0;
-        for (int d = 0; d < 3; ++d) {
-            ph0 += sk0[d] * xS[d];
-            ph1 += sk1[d] * xS[d];
-        }
-        double e0c, e0s, e1c, e1s;   // tile reference phases, float64
-        cis_rev(iota * ph0, e0c, e0s);
-        cis_rev(iota * ph1, e1c, e1s);
-        const double2 e0 = make_double2(e0c, e0s), e1 = make_double2(e1c, e1s);
-#pragma unroll
-        for (int r = 0; r < NT; ++r) {
-            a0r[r] += (double)b0r[r] * e0.x - (double)b0i[r] * e0.y;
-            a0i[r] += (double)b0r[r] * e0.y + (double)b0i[r] * e0.x;
-            a1r[r] += (double)b1r[r] * e1.x - (double)b1i[r] * e1.y;
-            a1i[r] += (double)b1r[r] * e1.y + (double)b1i[r] * e1.x;
         }
     }
 #pragma unroll
@@ -1100,28 +1202,27 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
 // ...: a capped grid leaves room on every CU for the kernels of the NUFFT
 // sub-problems running beside the direct sum on another stream.  Items stay
 // source-segment-major across consecutive workgroups either way.
-template <typename T, int NT>
+template <typename T, int NT, bool WIDE>
 __global__ __launch_bounds__(kDirectThreads) void k_direct(const DirectItem *__restrict__ items, int64_t nitems,
                                                            const double *__restrict__ sxyz, int64_t nsrc,
                                                            const double *__restrict__ txyz, int64_t ntgt,
                                                            const int32_t *__restrict__ perm,
                                                            const cplx<T> *__restrict__ in, int64_t in_stride,
                                                            double *__restrict__ acc, int64_t acc_stride, double iota,
-                                                           int det, const double2 *__restrict__ ctab)
+                                                           int det, int real_out, const double2 *__restrict__ ctab)
 {
     static_assert(kDirectSrcTile == kDirectThreads && kDirectTile == 2 * kDirectThreads, "direct tiling");
-    __shared__ double lx[kDirectSrcTile], ly[kDirectSrcTile], lz[kDirectSrcTile];
-    __shared__ cplx<T> lc[NT][kDirectSrcTile];
+    static_assert(kDirectSrcTile % 4 == 0, "the staged tile is walked in fours");
+    __shared__ __align__(16) double lx[kDirectSrcTile], ly[kDirectSrcTile], lz[kDirectSrcTile];
+    __shared__ __align__(16) cplx<T> lc[NT][kDirectSrcTile];
     __shared__ double2 ltab[sizeof(T) == 8 ? kCisTab : 1];   // float64 plans: the phase table
     if constexpr (sizeof(T) == 8) {
         for (int i = threadIdx.x; i < kCisTab; i += kDirectThreads) ltab[i] = ctab[i];
         // the first item's staging barrier orders these writes before any read
     }
-    for (int64_t w = blockIdx.x; w < nitems; w += gridDim.x) {
-        if (w != blockIdx.x) __syncthreads();   // the previous item's last tile is read before restaging
-        direct_item<T, NT>(items[w], sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc, acc_stride, iota, det, lx, ly,
-                           lz, lc, ltab);
-    }
+    for (int64_t w = blockIdx.x; w < nitems; w += gridDim.x)   // (staging starts with a barrier)
+        direct_item<T, NT, WIDE>(items[w], sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc, acc_stride, iota, det,
+                                 real_out, lx, ly, lz, lc, ltab);
 }
 
 // ---------------------------------------------------------------------------
@@ -1321,51 +1422,65 @@ hipError_t launch_interp(const PairDev *pairs, const int64_t *bprefix, int npair
     }
 }
 
-template <typename T, int NT>
+template <typename T, int NT, bool WIDE>
 static hipError_t launch_direct_rows(const DirectItem *items, int64_t nitems, const double *sxyz, int64_t nsrc,
                                      const double *txyz, int64_t ntgt, const int32_t *perm, const void *in,
                                      int64_t in_stride, double *acc, int64_t acc_stride, double iota, int det,
-                                     int64_t grid_cap, const void *ctab, hipStream_t st)
+                                     int real_out, int64_t grid_cap, const void *ctab, hipStream_t st)
 {
     const double2 *tab = static_cast<const double2 *>(ctab);
     if (grid_cap > 0) {
         // persistent: at most grid_cap workgroups looping over the items
         const int64_t nb = std::min<int64_t>(std::min<int64_t>(grid_cap, nitems), kMaxLaunchBlocks);
-        hipLaunchKernelGGL((k_direct<T, NT>), dim3(static_cast<unsigned>(nb)), dim3(kDirectThreads), 0, st, items,
-                           nitems, sxyz, nsrc, txyz, ntgt, perm, static_cast<const cplx<T> *>(in), in_stride, acc,
-                           acc_stride, iota, det, tab);
+        hipLaunchKernelGGL((k_direct<T, NT, WIDE>), dim3(static_cast<unsigned>(nb)), dim3(kDirectThreads), 0, st,
+                           items, nitems, sxyz, nsrc, txyz, ntgt, perm, static_cast<const cplx<T> *>(in), in_stride,
+                           acc, acc_stride, iota, det, real_out, tab);
         return hipGetLastError();
     }
     // one workgroup per item, in launches of at most kMaxLaunchBlocks workgroups
     // (a dispatch counts its work-items in 32 bits)
     for (int64_t i0 = 0; i0 < nitems; i0 += kMaxLaunchBlocks) {
         const int64_t nb = std::min<int64_t>(kMaxLaunchBlocks, nitems - i0);
-        hipLaunchKernelGGL((k_direct<T, NT>), dim3(static_cast<unsigned>(nb)), dim3(kDirectThreads), 0, st,
+        hipLaunchKernelGGL((k_direct<T, NT, WIDE>), dim3(static_cast<unsigned>(nb)), dim3(kDirectThreads), 0, st,
                            items + i0, nb, sxyz, nsrc, txyz, ntgt, perm, static_cast<const cplx<T> *>(in), in_stride,
-                           acc, acc_stride, iota, det, tab);
+                           acc, acc_stride, iota, det, real_out, tab);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
+template <typename T, int NT>
+static hipError_t launch_direct_wide(int wide, const DirectItem *items, int64_t nitems, const double *sxyz,
+                                     int64_t nsrc, const double *txyz, int64_t ntgt, const int32_t *perm,
+                                     const void *in, int64_t in_stride, double *acc, int64_t acc_stride, double iota,
+                                     int det, int real_out, int64_t grid_cap, const void *ctab, hipStream_t st)
+{
+    if constexpr (sizeof(T) == 4)
+        if (wide)
+            return launch_direct_rows<T, NT, true>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
+                                                   acc_stride, iota, det, real_out, grid_cap, ctab, st);
+    return launch_direct_rows<T, NT, false>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
+                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
+}
+
 template <typename T>
 hipError_t launch_direct(const DirectItem *items, int64_t nitems, const double *sxyz, int64_t nsrc,
                          const double *txyz, int64_t ntgt, const int32_t *perm, const void *in, int64_t in_stride,
-                         double *acc, int64_t acc_stride, int rows, double iota, int det, int64_t grid_cap,
-                         const void *ctab, hipStream_t st)
+                         double *acc, int64_t acc_stride, int rows, double iota, int det, int wide, int real_out,
+                         int64_t grid_cap, const void *ctab, hipStream_t st)
 {
     if (nitems <= 0) return hipSuccess;
     if (sizeof(T) == 8 && ctab == nullptr) return hipErrorInvalidValue;   // float64: the phase table
     switch (rows) {
-    case 1: return launch_direct_rows<T, 1>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, grid_cap, ctab, st);
-    case 2: return launch_direct_rows<T, 2>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, grid_cap, ctab, st);
-    case 3: return launch_direct_rows<T, 3>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, grid_cap, ctab, st);
-    case 4: return launch_direct_rows<T, 4>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, grid_cap, ctab, st);
+    case 1: return launch_direct_wide<T, 1>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
+                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
+    case 2: return launch_direct_wide<T, 2>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
+                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
+    case 3: return launch_direct_wide<T, 3>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
+                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
+    case 4: return launch_direct_wide<T, 4>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
+                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1406,10 +1521,10 @@ template hipError_t launch_interp<double>(const PairDev *, const int64_t *, int,
                                           double, int, hipStream_t);
 template hipError_t launch_direct<float>(const DirectItem *, int64_t, const double *, int64_t, const double *, int64_t,
                                          const int32_t *, const void *, int64_t, double *, int64_t, int, double, int,
-                                         int64_t, const void *, hipStream_t);
+                                         int, int, int64_t, const void *, hipStream_t);
 template hipError_t launch_direct<double>(const DirectItem *, int64_t, const double *, int64_t, const double *, int64_t,
                                           const int32_t *, const void *, int64_t, double *, int64_t, int, double, int,
-                                          int64_t, const void *, hipStream_t);
+                                          int, int, int64_t, const void *, hipStream_t);
 template <typename T>
 hipError_t launch_dde_scale(const void *w, const void *x, void *out, int64_t n, int terms, int conj_w, hipStream_t st)
 {

@@ -880,14 +880,18 @@ int make_host_plan(const double *uvw, int64_t n_vis, const double *xyz, int64_t 
 
     const double delta = p.dtype == HVOX_F64 ? 16.0 : 8.0;
     double Bw[3] = {0, 0, 0}, Pw[3] = {0, 0, 0};
+    double turns = 0.0;   // bound of every |<p_k, r_n>|
     for (int d = 0; d < 3; ++d) {
         double lo = INFINITY, hi = -INFINITY;
         for (int64_t i = 0; i < n_vis; ++i) { lo = std::min(lo, uvw[3 * i + d]); hi = std::max(hi, uvw[3 * i + d]); }
         Bw[d] = n_vis > 0 ? hi - lo : 0.0;
+        const double pmax = std::max(std::fabs(lo), std::fabs(hi));
         lo = INFINITY; hi = -INFINITY;
         for (int64_t i = 0; i < n_pix; ++i) { lo = std::min(lo, xyz[3 * i + d]); hi = std::max(hi, xyz[3 * i + d]); }
         Pw[d] = n_pix > 0 ? hi - lo : 0.0;
+        if (n_vis > 0 && n_pix > 0) turns += pmax * std::max(std::fabs(lo), std::fabs(hi));
     }
+    hp->wide_phase = turns <= kMaxMagicTurns ? 0 : 1;
     floor_widths(Bw, Pw, p.sigma);
 
     // Algorithm 1 for the current kernel widths (sets hp->h, hp->eta).
