@@ -40,11 +40,11 @@ template <typename T>
 hipError_t launch_interp(const PairDev *, const int64_t *, int, int64_t, const double *, int64_t, const double *,
                          const void *, int64_t, double *, int64_t, int, int, double, double, int, hipStream_t);
 template <typename T>
-hipError_t launch_direct(const DirectItem *, int64_t, const double *, int64_t, const double *, int64_t,
-                         const int32_t *, const void *, int64_t, double *, int64_t, int, double, int, int, int,
-                         int64_t, const void *, hipStream_t);
+hipError_t launch_direct(const DirectLaunch &, hipStream_t);
+hipError_t launch_add_layers(double *, int64_t, const double *, int, int, const int32_t *, int, int, hipStream_t);
 template <typename T>
-hipError_t launch_finalize(const double *, int64_t, const int32_t *, void *, int, hipStream_t);
+hipError_t launch_finalize(const double *, int64_t, const int32_t *, void *, int, const double *, int, int,
+                           const int32_t *, int, hipStream_t);
 template <typename T>
 hipError_t launch_dde_scale(const void *, const void *, void *, int64_t, int, int, hipStream_t);
 template <typename T>
@@ -64,6 +64,7 @@ struct DevDir {
     PairDev *pairs = nullptr;
     int64_t *pre_pts = nullptr, *pre_tgts = nullptr, *pre_tiles[3] = {nullptr, nullptr, nullptr};
     DirectItem *direct = nullptr;
+    int32_t *tgt_layers = nullptr;   // stored direct sums: layers of every target
     double *deconv = nullptr;        // per chunk-order target
     int64_t *pre_ttiles = nullptr;   // per batch: transpose-tile prefix over its pairs
     int32_t *records = nullptr;      // source indices listed per tile (plan-resident binning)
@@ -103,6 +104,7 @@ struct hvox_plan_s {
     void *ws = nullptr;
     void *stage = nullptr;                              // staged sources of one batch (value and footprint)
     double *acc = nullptr;
+    double *slab = nullptr;                             // direct sums stored by layer
     hipStream_t last_stream = nullptr;
     // a second stream (default priority) the direct sum runs on while the NUFFT
     // batches run on the caller's stream, forked and joined with two events
@@ -256,6 +258,7 @@ struct Scratch {
     void *stage;
     double *acc;
     void *xval;   // staged values of rows 1 .. rows-1 of a NUFFT pass
+    double *slab; // direct sums stored by layer (hp.slab_elems complex values; NULL: layers add in place)
 };
 
 // ---- executor -----------------------------------------------------------------
@@ -312,20 +315,24 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
     for (int32_t t0 = 0; t0 < ntrans; t0 += kRowBatch) {
         const int nb = static_cast<int>(std::min<int32_t>(kRowBatch, ntrans - t0));
         if (n_tgt == 0) continue;
-        HVOX_TRY(timed(pl, may_time, HVOX_K_ZERO, st, [&] { return launch_zero(sc.acc, 2 * n_tgt * nb, st); }));
+        // layers of direct items per launch whose sums fit the slabs (0: items add into the accumulator).
+        // Deterministic plans take what fits; others need every layer, or add with atomics
+        const int64_t fit = sc.slab && dp.slab_layers > 0 ? hp.slab_elems / (n_tgt * nb) : 0;
+        const int64_t group = det ? std::min(fit, dp.layers) : (fit >= dp.layers ? dp.layers : 0);
+        DirectLaunch dl{dd.direct, 0, dp.direct_tile, sxyz, n_src, txyz, n_tgt, sperm,
+                        static_cast<const C *>(in) + static_cast<int64_t>(t0) * n_src, sc.acc, nb, iota, kDirectAtomic,
+                        0, 0, hp.wide_phase, real_only, 0, pl->cis_tab};
+        // stored sums alone make the result when there is nothing else to add: no accumulator
+        bool fresh = group > 0 && dp.batches.empty();
+        if (!fresh)
+            HVOX_TRY(timed(pl, may_time, HVOX_K_ZERO, st, [&] { return launch_zero(sc.acc, 2 * n_tgt * nb, st); }));
         if (overlap) {
             // fork: the direct sum starts once the accumulator is clear
             HVOX_TRY(hipEventRecord(pl->fork_ev, st));
             HVOX_TRY(hipStreamWaitEvent(pl->side, pl->fork_ev, 0));
-            for (size_t l = 0; l + 1 < dp.direct_layer_off.size(); ++l) {
-                const int64_t i0 = dp.direct_layer_off[l], i1 = dp.direct_layer_off[l + 1];
-                HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, dst, [&] {
-                    return launch_direct<T>(dd.direct + i0, i1 - i0, sxyz, n_src, txyz, n_tgt, sperm,
-                                            static_cast<const C *>(in) + static_cast<int64_t>(t0) * n_src, n_src,
-                                            sc.acc, 2 * n_tgt, nb, iota, det, hp.wide_phase, real_only, direct_cap,
-                                            pl->cis_tab, dst);
-                }));
-            }
+            dl.nitems = static_cast<int64_t>(dp.direct.size());
+            dl.grid_cap = direct_cap;
+            HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, dst, [&] { return launch_direct<T>(dl, dst); }));
             HVOX_TRY(hipEventRecord(pl->join_ev, pl->side));
         }
         // NUFFT sub-problems: passes of up to hp.rows data rows, each pass sharing the
@@ -371,24 +378,44 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
                 }));
             }
         }
-        // direct blocks (unless already on the second stream): one launch, or
-        // (deterministic plans) one launch per layer of items that share no
-        // target, in a fixed order
-        if (overlap) HVOX_TRY(hipStreamWaitEvent(st, pl->join_ev, 0));   // join before the finalize
-        else for (size_t l = 0; l + 1 < dp.direct_layer_off.size(); ++l) {
-            const int64_t i0 = dp.direct_layer_off[l], i1 = dp.direct_layer_off[l + 1];
-            HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, st, [&] {
-                return launch_direct<T>(dd.direct + i0, i1 - i0, sxyz, n_src, txyz, n_tgt, sperm,
-                                        static_cast<const C *>(in) + static_cast<int64_t>(t0) * n_src, n_src, sc.acc,
-                                        2 * n_tgt, nb, iota, det, hp.wide_phase, real_only, 0, pl->cis_tab, st);
-            }));
+        // direct blocks (unless already on the second stream): launches of `group` layers
+        // that store their sums, one launch of atomic adds, or (deterministic plans without
+        // slabs) one launch per layer of items that share no target, in a fixed order
+        const double *slab = nullptr;
+        int layer0 = 0;
+        const int64_t nl = static_cast<int64_t>(dp.direct_layer_off.size()) - 1;
+        if (overlap) {
+            HVOX_TRY(hipStreamWaitEvent(st, pl->join_ev, 0));   // join before the finalize
+        } else if (group > 0) {
+            dl.store = kDirectSlab;
+            dl.acc = sc.slab;
+            dl.layers = static_cast<int>(group);
+            for (int64_t l0 = 0; l0 < dp.layers; l0 += group) {
+                if (l0 > 0) {   // the slabs are needed again: their layers go to the accumulator
+                    HVOX_TRY(launch_add_layers(sc.acc, n_tgt, sc.slab, layer0, dl.layers, dd.tgt_layers, fresh, nb, st));
+                    fresh = false;
+                }
+                layer0 = dl.layer0 = static_cast<int>(l0);
+                const int64_t i0 = dp.direct_layer_off[det ? l0 : 0];
+                const int64_t i1 = dp.direct_layer_off[det ? std::min(l0 + group, nl) : nl];
+                dl.items = dd.direct + i0;
+                dl.nitems = i1 - i0;
+                HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, st, [&] { return launch_direct<T>(dl, st); }));
+            }
+            slab = sc.slab;
+        } else {
+            dl.store = det ? kDirectAdd : kDirectAtomic;
+            for (int64_t l = 0; l < nl; ++l) {
+                dl.items = dd.direct + dp.direct_layer_off[l];
+                dl.nitems = dp.direct_layer_off[l + 1] - dp.direct_layer_off[l];
+                HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, st, [&] { return launch_direct<T>(dl, st); }));
+            }
         }
-        for (int r = 0; r < nb; ++r) {
-            C *out_t = static_cast<C *>(out) + static_cast<int64_t>(t0 + r) * n_tgt;
-            HVOX_TRY(timed(pl, may_time, HVOX_K_FINAL, st, [&] {
-                return launch_finalize<T>(sc.acc + 2 * n_tgt * r, n_tgt, tperm, out_t, real_only, st);
-            }));
-        }
+        HVOX_TRY(timed(pl, may_time, HVOX_K_FINAL, st, [&] {
+            return launch_finalize<T>(fresh ? nullptr : sc.acc, n_tgt, tperm,
+                                      static_cast<C *>(out) + static_cast<int64_t>(t0) * n_tgt, real_only, slab, layer0,
+                                      static_cast<int>(group), dd.tgt_layers, nb, st);
+        }));
         for (int k = 0; k < HVOX_K_COUNT; ++k) {
             pl->stats.alg_bytes[k] += dp.alg_bytes[k] * nb;
             pl->stats.alg_flops[k] += dp.alg_flops[k] * nb;
@@ -406,7 +433,7 @@ Scratch plan_scratch(const hvox_plan_s *pl)
     int64_t rec_b, val_b;
     stage_layout(pl->hp, &rec_b, &val_b);
     void *xval = pl->stage && val_b > 0 ? static_cast<char *>(pl->stage) + rec_b : nullptr;
-    return Scratch{pl->ws, pl->stage, pl->acc, xval};
+    return Scratch{pl->ws, pl->stage, pl->acc, xval, pl->slab};
 }
 
 int transform(hvox_plan_s *pl, bool synthesis, const void *in, void *out, int32_t ntrans, void *stream)
@@ -484,6 +511,7 @@ int upload_dir(hvox_plan_s *pl, const DirPlan &dp, DevDir *dd, hipStream_t st)
     for (int q = 0; q < 3; ++q)
         if ((e = upload(pl, dp.pre_tiles[q], &dd->pre_tiles[q], st)) != hipSuccess) return HVOX_ERR_OOM;
     if ((e = upload(pl, dp.direct, &dd->direct, st)) != hipSuccess) return HVOX_ERR_OOM;
+    if ((e = upload(pl, dp.tgt_layers, &dd->tgt_layers, st)) != hipSuccess) return HVOX_ERR_OOM;
     if ((e = upload(pl, dp.pre_ttiles, &dd->pre_ttiles, st)) != hipSuccess) return HVOX_ERR_OOM;
     return HVOX_OK;
 }
@@ -767,6 +795,8 @@ int build_device(hvox_plan_s *pl, hipStream_t st, std::string *err)
                   true, st),
         "accumulator");
     pl->acc = static_cast<double *>(tmp);
+    chk(dev_alloc(pl, 16 * static_cast<size_t>(hp.slab_elems), &tmp, true, st), "direct-sum slabs");
+    pl->slab = static_cast<double *>(tmp);
     chk(dev_alloc(pl, delta * static_cast<size_t>(hp.ws_elems), &pl->ws, false, st), "workspace");
     int64_t rec_b, val_b;
     stage_layout(hp, &rec_b, &val_b);
@@ -859,8 +889,12 @@ int transform_static(hvox_plan_s *pl, int32_t direction, const void *in, void *o
     char *b = static_cast<char *>(base);
     int64_t rec_b, val_b;
     stage_layout(hp, &rec_b, &val_b);
+    // (the slabs of stored direct sums where they fit too; else items add in place)
+    const size_t slab_b = 16 * static_cast<size_t>(hp.slab_elems);
     const Scratch sc{b + acc_b + stage_b, b + acc_b, reinterpret_cast<double *>(b),
-                     val_b > 0 ? b + acc_b + rec_b : nullptr};
+                     val_b > 0 ? b + acc_b + rec_b : nullptr,
+                     slab_b <= HVOX_STATIC_SCRATCH_BYTES - (acc_b + stage_b + ws_b)
+                         ? reinterpret_cast<double *>(b + acc_b + stage_b + ws_b) : nullptr};
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (f64) return run_direction<double>(pl, synthesis, in, out, ntrans, st, sc, false);
     return run_direction<float>(pl, synthesis, in, out, ntrans, st, sc, false);
@@ -1057,7 +1091,7 @@ int hvox_plan_upload(hvox_plan_t plan, void *stream)
         plan->vis_xyz = plan->sky_xyz = nullptr;
         plan->vis_perm = plan->sky_perm = nullptr;
         plan->precor = plan->tw = plan->ws = plan->stage = plan->cis_tab = nullptr;
-        plan->acc = nullptr;
+        plan->acc = plan->slab = nullptr;
         plan->syn = DevDir{};
         plan->ana = DevDir{};
         return fail(rc, err);
@@ -1146,6 +1180,8 @@ int hvox_plan_info(hvox_plan_t plan, hvox_plan_info_t *out)
     out->flags = hp.prm.flags;
     out->on_device = plan->host_only ? 0 : 1;
     out->n_direct_layers = static_cast<int64_t>(std::max<size_t>(hp.syn.direct_layer_off.size(), 1) - 1);
+    if (hp.prm.deterministic() && hp.syn.slab_layers > 0)   // launches of slab_layers layers
+        out->n_direct_layers = (hp.syn.layers + hp.syn.slab_layers - 1) / hp.syn.slab_layers;
     size_t acc_b, stage_b, ws_b;
     static_scratch_layout(hp, &acc_b, &stage_b, &ws_b);
     out->noalloc_scratch_bytes = static_cast<int64_t>(acc_b + stage_b + ws_b);

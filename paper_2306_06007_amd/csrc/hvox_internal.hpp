@@ -34,9 +34,18 @@ constexpr int fft_lds_stride(int n) { return n + 1; }
 constexpr int fft_lds_elems(int lines, int n) { return lines * fft_lds_stride(n); }
 constexpr int kDirectThreads = 256;  // threads of a direct-sum workgroup
 constexpr int kDirectTile = 512;     // targets per direct-sum workgroup (two per thread)
+constexpr int kDirectNarrow = 128;   // the same where wide tiles leave the GPU idle: the wavefronts divide the sources
 constexpr int kDirectSrcTile = 256;  // sources staged in LDS at a time
 constexpr int kDirectSeg = 8192;     // longest source segment of a direct-sum work item
 constexpr int64_t kDirectMinItems = 4096;   // shorter segments while a plan has fewer direct work items
+// a direction whose wide tiles give fewer items than this (four per CU) at the shortest
+// wide segment takes narrow tiles and segments down to kDirectNarrowSeg
+constexpr int64_t kDirectFewItems = 1024;
+constexpr int kDirectNarrowSeg = 128;
+// partial sums that direct items store instead of adding them up (complex float64 values
+// per data row): whole directions without NUFFT sub-problems, groups of layers in
+// deterministic plans
+constexpr int64_t kSlabElems = int64_t(1) << 20, kSlabElemsDet = int64_t(1) << 22;
 constexpr int kDirectWgPerCu = 8;    // direct-sum workgroups per CU while NUFFT work runs beside it
 // float32 direct sum: phases of at most this many turns take their fraction from the
 // low word of a float64 sum (kernels.hip, kPhaseMagic); larger ones through a float64 fraction
@@ -133,8 +142,33 @@ static_assert(kFftMaxLen < 32768, "tile corners are stored in 16 bits");
 struct DirectItem {
     int64_t tgt_off;             // chunk-order index of the first target
     int64_t src_off;             // chunk-order index of the first source
-    int32_t tgt_cnt;
-    int32_t src_cnt;
+    int32_t layer;               // position of its source segment among those of its targets
+    int16_t tgt_cnt;
+    int16_t src_cnt;
+};
+static_assert(sizeof(DirectItem) == 24 && kDirectSeg < 32768 && kDirectTile < 32768, "direct item layout");
+// what a direct item does with its sums
+enum DirectStore { kDirectAtomic, kDirectAdd, kDirectSlab };
+
+// ---- a launch of the direct sum: rows data rows of `items` --------------------
+struct DirectLaunch {
+    const DirectItem *items;
+    int64_t nitems;
+    int tile;                    // targets per item
+    const double *sxyz;          // sources, targets: SoA, chunk order
+    int64_t nsrc;
+    const double *txyz;
+    int64_t ntgt;
+    const int32_t *perm;         // chunk order -> position in `in` (NULL: already in chunk order)
+    const void *in;              // [rows][nsrc]
+    double *acc;                 // accumulator [rows][ntgt], or slabs [rows][layers][ntgt] (complex)
+    int rows;
+    double iota;
+    int store;                   // DirectStore
+    int layer0, layers;          // kDirectSlab: first layer of the launch, layers of a row's slabs
+    int wide_phase, real_out;
+    int64_t grid_cap;            // > 0: persistent grid of at most this many workgroups
+    const void *ctab;            // float64 plans: the phase table
 };
 
 // ---- host-side plan pieces -------------------------------------------------
@@ -182,9 +216,15 @@ struct DirPlan {                         // one direction (synthesis or analysis
     std::vector<DirectItem> direct;
     // direct items in launch order: [direct_layer_off[l], direct_layer_off[l + 1]) is launch l.
     // One launch of every item unless the plan is deterministic: then layer l holds the l-th
-    // source segment of every target tile, so the items of a launch never share a target and
-    // add into the accumulator without atomics, layer after layer.
+    // source segment of every target tile, so the items of a layer never share a target and
+    // layers add up in a fixed order.
     std::vector<int64_t> direct_layer_off;
+    int direct_tile = kDirectTile;           // targets per item (kDirectTile or kDirectNarrow)
+    // layers whose items may run in one launch, each storing its sums in a slab of its own that
+    // is added up afterwards, layer after layer (0: items add into the accumulator), the layers in
+    // all, and those of every target (chunk order, device copy released after the upload)
+    int64_t slab_layers = 0, layers = 0;
+    std::vector<int32_t> tgt_layers;
     double grid_cells = 0.0, direct_terms = 0.0;
     int64_t occ_tiles[2] = {0, 0}, occ_xlines[2] = {0, 0}, occ_zplanes[2] = {0, 0};   // filled by the binning
     double est_seconds = 0.0;
@@ -230,6 +270,7 @@ struct HostPlan {
     int rows = 1;
     int64_t ws_row = 0;
     int64_t max_pts = 0;                 // spread points of the largest batch
+    int64_t slab_elems = 0;              // complex float64 values of the direct sum's slabs
     int wide_phase = 0;                  // 1: some phase may exceed kMaxMagicTurns
     // unique FFT-length tables: (n1, n2) pre-correction tables and n2 twiddles
     std::vector<double> precor_nu;       // nu = l / n2 of every pre-correction entry

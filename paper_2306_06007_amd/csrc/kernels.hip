@@ -1099,19 +1099,25 @@ __device__ __forceinline__ void direct_tile(int jb, int je, const double q0[3], 
     }
 }
 
-template <typename T, int NT, bool WIDE>
+template <typename T, int NT, int TILE, bool WIDE>
 __device__ __forceinline__ void direct_item(const DirectItem it, const double *__restrict__ sxyz, int64_t nsrc,
                                             const double *__restrict__ txyz, int64_t ntgt,
                                             const int32_t *__restrict__ perm, const cplx<T> *__restrict__ in,
                                             int64_t in_stride, double *__restrict__ acc, int64_t acc_stride,
-                                            double iota, int det, int real_out, double *lx, double *ly, double *lz,
-                                            cplx<T> (*lc)[kDirectSrcTile], const double2 *ltab)
+                                            double iota, int store, int layer0, int layers, int real_out,
+                                            double (*lxyz)[kDirectSrcTile], cplx<T> (*lc)[kDirectSrcTile],
+                                            const double2 *ltab)
 {
-    const int tid = threadIdx.x;
+    // TILE / 2 threads hold the targets; SL such slices divide the staged sources
+    constexpr int kHalf = TILE / 2, SL = kDirectThreads / kHalf;
+    static_assert(kHalf % 64 == 0 && SL * kHalf == kDirectThreads, "a wavefront lies in one slice");
+    const int tid = threadIdx.x, tl = SL == 1 ? tid : tid & (kHalf - 1);
+    const int slice = SL == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / kHalf);
+    double *lx = lxyz[0], *ly = lxyz[1], *lz = lxyz[2];
     // two targets per thread: each staged source is read from LDS once for both
-    const bool has0 = tid < it.tgt_cnt, has1 = tid + kDirectThreads < it.tgt_cnt;
-    const int64_t k0 = it.tgt_off + (has0 ? tid : 0);
-    const int64_t k1 = it.tgt_off + (has1 ? tid + kDirectThreads : 0);
+    const bool has0 = tl < it.tgt_cnt, has1 = tl + kHalf < it.tgt_cnt;
+    const int64_t k0 = it.tgt_off + (has0 ? tl : 0);
+    const int64_t k1 = it.tgt_off + (has1 ? tl + kHalf : 0);
     constexpr bool kRef = sizeof(T) == 8;   // phases relative to the staged tile's first source
     const double unit = kRef ? iota * kCisTab : iota;   // the sign enters through the phase
     double q0[3], q1[3];
@@ -1146,20 +1152,21 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
             }
         }
         const bool cplx_in = __syncthreads_or(im);
-        const int je = (cnt + 3) & ~3;
+        const int c4 = (cnt + 3) & ~3, per = (c4 / 4 + SL - 1) / SL * 4;   // this slice's share
+        const int jb = SL == 1 ? 0 : min(slice * per, c4), je = SL == 1 ? c4 : min(jb + per, c4);
         if constexpr (!kRef) {
             if (real_out)
-                direct_tile<T, NT, WIDE, kDirectRealOut>(0, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
+                direct_tile<T, NT, WIDE, kDirectRealOut>(jb, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
             else if (cplx_in)
-                direct_tile<T, NT, WIDE, kDirectComplex>(0, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
-            else direct_tile<T, NT, WIDE, kDirectRealIn>(0, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
+                direct_tile<T, NT, WIDE, kDirectComplex>(jb, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
+            else direct_tile<T, NT, WIDE, kDirectRealIn>(jb, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
         } else {
             double b0r[NT], b0i[NT], b1r[NT], b1i[NT];
 #pragma unroll
             for (int r = 0; r < NT; ++r) b0r[r] = b0i[r] = b1r[r] = b1i[r] = 0.0;
             if (cplx_in)
-                direct_tile<T, NT, WIDE, kDirectComplex>(0, je, q0, q1, lx, ly, lz, lc, ltab, b0r, b0i, b1r, b1i);
-            else direct_tile<T, NT, WIDE, kDirectRealIn>(0, je, q0, q1, lx, ly, lz, lc, ltab, b0r, b0i, b1r, b1i);
+                direct_tile<T, NT, WIDE, kDirectComplex>(jb, je, q0, q1, lx, ly, lz, lc, ltab, b0r, b0i, b1r, b1i);
+            else direct_tile<T, NT, WIDE, kDirectRealIn>(jb, je, q0, q1, lx, ly, lz, lc, ltab, b0r, b0i, b1r, b1i);
             // tile reference phases (q / kCisTab is exact)
             double p0[3], p1[3], e0c, e0s, e1c, e1s;
             for (int d = 0; d < 3; ++d) {
@@ -1177,11 +1184,41 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
             }
         }
     }
+    // add the slices, halving their number: the upper half hands its sums over
+    if constexpr (SL > 1) {
+        double2 *red = reinterpret_cast<double2 *>(lxyz);
+        static_assert(sizeof(double2) * (SL / 2) * TILE <= 3 * sizeof(double) * kDirectSrcTile, "the sums fit the stage");
+#pragma unroll
+        for (int r = 0; r < NT; ++r) {
+#pragma unroll
+            for (int h = SL / 2; h > 0; h /= 2) {
+                __syncthreads();
+                if (slice >= h && slice < 2 * h) {
+                    red[(slice - h) * TILE + tl] = make_double2(a0r[r], a0i[r]);
+                    red[(slice - h) * TILE + kHalf + tl] = make_double2(a1r[r], a1i[r]);
+                }
+                __syncthreads();
+                if (slice < h) {
+                    const double2 v0 = red[slice * TILE + tl], v1 = red[slice * TILE + kHalf + tl];
+                    a0r[r] += v0.x;
+                    a0i[r] += v0.y;
+                    a1r[r] += v1.x;
+                    a1i[r] += v1.y;
+                }
+            }
+        }
+        if (slice > 0) return;
+    }
 #pragma unroll
     for (int r = 0; r < NT; ++r) {
         double *ar = acc + r * acc_stride;
-        if (det) {
-            // deterministic plans launch items sharing no target together (one layer)
+        if (store == kDirectSlab) {
+            // the sums of this layer, added up afterwards (acc: the slabs)
+            double2 *sl = reinterpret_cast<double2 *>(acc) + ((int64_t)r * layers + (it.layer - layer0)) * ntgt;
+            if (has0) sl[k0] = make_double2(a0r[r], a0i[r]);
+            if (has1) sl[k1] = make_double2(a1r[r], a1i[r]);
+        } else if (store == kDirectAdd) {
+            // items of one layer: no other workgroup of this launch adds to these targets
             if (has0) { ar[2 * k0] += a0r[r]; ar[2 * k0 + 1] += a0i[r]; }
             if (has1) { ar[2 * k1] += a1r[r]; ar[2 * k1 + 1] += a1i[r]; }
         } else {
@@ -1202,18 +1239,19 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
 // ...: a capped grid leaves room on every CU for the kernels of the NUFFT
 // sub-problems running beside the direct sum on another stream.  Items stay
 // source-segment-major across consecutive workgroups either way.
-template <typename T, int NT, bool WIDE>
+template <typename T, int NT, int TILE, bool WIDE>
 __global__ __launch_bounds__(kDirectThreads) void k_direct(const DirectItem *__restrict__ items, int64_t nitems,
                                                            const double *__restrict__ sxyz, int64_t nsrc,
                                                            const double *__restrict__ txyz, int64_t ntgt,
                                                            const int32_t *__restrict__ perm,
                                                            const cplx<T> *__restrict__ in, int64_t in_stride,
                                                            double *__restrict__ acc, int64_t acc_stride, double iota,
-                                                           int det, int real_out, const double2 *__restrict__ ctab)
+                                                           int store, int layer0, int layers, int real_out,
+                                                           const double2 *__restrict__ ctab)
 {
     static_assert(kDirectSrcTile == kDirectThreads && kDirectTile == 2 * kDirectThreads, "direct tiling");
     static_assert(kDirectSrcTile % 4 == 0, "the staged tile is walked in fours");
-    __shared__ __align__(16) double lx[kDirectSrcTile], ly[kDirectSrcTile], lz[kDirectSrcTile];
+    __shared__ __align__(16) double lxyz[3][kDirectSrcTile];
     __shared__ __align__(16) cplx<T> lc[NT][kDirectSrcTile];
     __shared__ double2 ltab[sizeof(T) == 8 ? kCisTab : 1];   // float64 plans: the phase table
     if constexpr (sizeof(T) == 8) {
@@ -1221,21 +1259,62 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct(const DirectItem *__r
         // the first item's staging barrier orders these writes before any read
     }
     for (int64_t w = blockIdx.x; w < nitems; w += gridDim.x)   // (staging starts with a barrier)
-        direct_item<T, NT, WIDE>(items[w], sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc, acc_stride, iota, det,
-                                 real_out, lx, ly, lz, lc, ltab);
+        direct_item<T, NT, TILE, WIDE>(items[w], sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc, acc_stride, iota,
+                                       store, layer0, layers, real_out, lxyz, lc, ltab);
 }
 
 // ---------------------------------------------------------------------------
-// epilogue: cast the float64 accumulator to the plan's precision and scatter
-// to user order (the inverse of the chunk-order gather, Sect. 4 Fig. 5).
+// sums that direct items stored by layer: the accumulator takes layers
+// [layer0, layer0 + layers) of every target in order (tgt_layers: layers of a
+// target in all), after what it holds or (fresh) from zero.  Grid y: data rows.
+// ---------------------------------------------------------------------------
+__global__ void k_add_layers(double2 *__restrict__ acc, int64_t n, const double2 *__restrict__ slab, int layer0,
+                             int layers, const int32_t *__restrict__ tgt_layers, int fresh)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    acc += blockIdx.y * n;
+    slab += (int64_t)blockIdx.y * layers * n;
+    double2 v = fresh ? make_double2(0.0, 0.0) : acc[k];
+    const int m = min(layers, tgt_layers[k] - layer0);
+    for (int l = 0; l < m; ++l) {
+        const double2 s = slab[l * n + k];
+        v.x += s.x;
+        v.y += s.y;
+    }
+    acc[k] = v;
+}
+
+// ---------------------------------------------------------------------------
+// epilogue: cast the float64 sums to the plan's precision and scatter to user
+// order (the inverse of the chunk-order gather, Sect. 4 Fig. 5).  The sums are
+// the accumulator (if any) and the last stored layers (if any); G = 1 << lg lanes share
+// a target's layers, each every G-th of them, so that few targets with many
+// layers still fill the GPU.  Grid y: data rows.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void k_finalize(const double *__restrict__ acc, int64_t n, const int32_t *__restrict__ perm,
-                           cplx<T> *__restrict__ out, int real_only)
+__global__ void k_finalize(const double2 *__restrict__ acc, int64_t n, const int32_t *__restrict__ perm,
+                           cplx<T> *__restrict__ out, int real_only, const double2 *__restrict__ slab, int layer0,
+                           int layers, const int32_t *__restrict__ tgt_layers, int lg)
 {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    out[perm ? perm[k] : k] = mk<T>(T(acc[2 * k]), real_only ? T(0) : T(acc[2 * k + 1]));
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, k = t >> lg;
+    const int g = (int)(t & ((1 << lg) - 1));
+    if (k >= n) return;   // (whole groups)
+    double2 v = acc && g == 0 ? acc[blockIdx.y * n + k] : make_double2(0.0, 0.0);
+    if (slab) {
+        slab += (int64_t)blockIdx.y * layers * n + k;
+        const int m = min(layers, tgt_layers[k] - layer0);
+        for (int l = g; l < m; l += 1 << lg) {
+            const double2 s = slab[l * n];
+            v.x += s.x;
+            v.y += s.y;
+        }
+        for (int off = 1 << lg >> 1; off > 0; off >>= 1) {
+            v.x += __shfl_xor(v.x, off, 64);
+            v.y += __shfl_xor(v.y, off, 64);
+        }
+    }
+    if (g == 0) out[blockIdx.y * n + (perm ? perm[k] : k)] = mk<T>(T(v.x), real_only ? T(0) : T(v.y));
 }
 
 // ---------------------------------------------------------------------------
@@ -1422,76 +1501,79 @@ hipError_t launch_interp(const PairDev *pairs, const int64_t *bprefix, int npair
     }
 }
 
-template <typename T, int NT, bool WIDE>
-static hipError_t launch_direct_rows(const DirectItem *items, int64_t nitems, const double *sxyz, int64_t nsrc,
-                                     const double *txyz, int64_t ntgt, const int32_t *perm, const void *in,
-                                     int64_t in_stride, double *acc, int64_t acc_stride, double iota, int det,
-                                     int real_out, int64_t grid_cap, const void *ctab, hipStream_t st)
+// arguments of a direct-sum launch
+template <typename T, int NT, int TILE, bool WIDE>
+static hipError_t direct_grid(const DirectLaunch &d, hipStream_t st)
 {
-    const double2 *tab = static_cast<const double2 *>(ctab);
-    if (grid_cap > 0) {
-        // persistent: at most grid_cap workgroups looping over the items
-        const int64_t nb = std::min<int64_t>(std::min<int64_t>(grid_cap, nitems), kMaxLaunchBlocks);
-        hipLaunchKernelGGL((k_direct<T, NT, WIDE>), dim3(static_cast<unsigned>(nb)), dim3(kDirectThreads), 0, st,
-                           items, nitems, sxyz, nsrc, txyz, ntgt, perm, static_cast<const cplx<T> *>(in), in_stride,
-                           acc, acc_stride, iota, det, real_out, tab);
+    if (d.nitems > kMaxLaunchBlocks * (int64_t(1) << 20)) return hipErrorInvalidValue;
+    auto go = [&](const DirectItem *items, int64_t n, int64_t grid) {
+        hipLaunchKernelGGL((k_direct<T, NT, TILE, WIDE>), dim3(static_cast<unsigned>(grid)), dim3(kDirectThreads), 0, st,
+                           items, n, d.sxyz, d.nsrc, d.txyz, d.ntgt, d.perm, static_cast<const cplx<T> *>(d.in), d.nsrc,
+                           d.acc, 2 * d.ntgt, d.iota, d.store, d.layer0, d.layers, d.real_out,
+                           static_cast<const double2 *>(d.ctab));
         return hipGetLastError();
-    }
+    };
+    // persistent: at most grid_cap workgroups looping over the items
+    if (d.grid_cap > 0)
+        return go(d.items, d.nitems, std::min<int64_t>(std::min<int64_t>(d.grid_cap, d.nitems), kMaxLaunchBlocks));
     // one workgroup per item, in launches of at most kMaxLaunchBlocks workgroups
     // (a dispatch counts its work-items in 32 bits)
-    for (int64_t i0 = 0; i0 < nitems; i0 += kMaxLaunchBlocks) {
-        const int64_t nb = std::min<int64_t>(kMaxLaunchBlocks, nitems - i0);
-        hipLaunchKernelGGL((k_direct<T, NT, WIDE>), dim3(static_cast<unsigned>(nb)), dim3(kDirectThreads), 0, st,
-                           items + i0, nb, sxyz, nsrc, txyz, ntgt, perm, static_cast<const cplx<T> *>(in), in_stride,
-                           acc, acc_stride, iota, det, real_out, tab);
-        const hipError_t e = hipGetLastError();
+    for (int64_t i0 = 0; i0 < d.nitems; i0 += kMaxLaunchBlocks) {
+        const int64_t nb = std::min<int64_t>(kMaxLaunchBlocks, d.nitems - i0);
+        const hipError_t e = go(d.items + i0, nb, nb);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 template <typename T, int NT>
-static hipError_t launch_direct_wide(int wide, const DirectItem *items, int64_t nitems, const double *sxyz,
-                                     int64_t nsrc, const double *txyz, int64_t ntgt, const int32_t *perm,
-                                     const void *in, int64_t in_stride, double *acc, int64_t acc_stride, double iota,
-                                     int det, int real_out, int64_t grid_cap, const void *ctab, hipStream_t st)
+static hipError_t direct_shape(const DirectLaunch &d, hipStream_t st)
 {
+    const bool narrow = d.tile == kDirectNarrow;
     if constexpr (sizeof(T) == 4)
-        if (wide)
-            return launch_direct_rows<T, NT, true>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                                   acc_stride, iota, det, real_out, grid_cap, ctab, st);
-    return launch_direct_rows<T, NT, false>(items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
+        if (d.wide_phase)
+            return narrow ? direct_grid<T, NT, kDirectNarrow, true>(d, st) : direct_grid<T, NT, kDirectTile, true>(d, st);
+    return narrow ? direct_grid<T, NT, kDirectNarrow, false>(d, st) : direct_grid<T, NT, kDirectTile, false>(d, st);
 }
 
 template <typename T>
-hipError_t launch_direct(const DirectItem *items, int64_t nitems, const double *sxyz, int64_t nsrc,
-                         const double *txyz, int64_t ntgt, const int32_t *perm, const void *in, int64_t in_stride,
-                         double *acc, int64_t acc_stride, int rows, double iota, int det, int wide, int real_out,
-                         int64_t grid_cap, const void *ctab, hipStream_t st)
+hipError_t launch_direct(const DirectLaunch &d, hipStream_t st)
 {
-    if (nitems <= 0) return hipSuccess;
-    if (sizeof(T) == 8 && ctab == nullptr) return hipErrorInvalidValue;   // float64: the phase table
-    switch (rows) {
-    case 1: return launch_direct_wide<T, 1>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
-    case 2: return launch_direct_wide<T, 2>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
-    case 3: return launch_direct_wide<T, 3>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
-    case 4: return launch_direct_wide<T, 4>(wide, items, nitems, sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc,
-                                            acc_stride, iota, det, real_out, grid_cap, ctab, st);
+    if (d.nitems <= 0) return hipSuccess;
+    if (sizeof(T) == 8 && d.ctab == nullptr) return hipErrorInvalidValue;   // float64: the phase table
+    if (d.tile != kDirectTile && d.tile != kDirectNarrow) return hipErrorInvalidValue;
+    switch (d.rows) {
+    case 1: return direct_shape<T, 1>(d, st);
+    case 2: return direct_shape<T, 2>(d, st);
+    case 3: return direct_shape<T, 3>(d, st);
+    case 4: return direct_shape<T, 4>(d, st);
     default: return hipErrorInvalidValue;
     }
 }
 
+hipError_t launch_add_layers(double *acc, int64_t n, const double *slab, int layer0, int layers,
+                             const int32_t *tgt_layers, int fresh, int rows, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_add_layers, dim3(blocks_for(n, 256, INT32_MAX), static_cast<unsigned>(rows)), dim3(256), 0, st,
+                       reinterpret_cast<double2 *>(acc), n, reinterpret_cast<const double2 *>(slab), layer0, layers,
+                       tgt_layers, fresh);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_finalize(const double *acc, int64_t n, const int32_t *perm, void *out, int real_only,
+                           const double *slab, int layer0, int layers, const int32_t *tgt_layers, int rows,
                            hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finalize<T>, dim3(blocks_for(n, 256, INT32_MAX)), dim3(256), 0, st, acc, n, perm,
-                       static_cast<cplx<T> *>(out), real_only);
+    // lanes per target: up to a wavefront, while the targets alone do not fill the GPU
+    // (2^18 threads) and every lane keeps two layers
+    int lg = 0;
+    while (slab && lg < 6 && (n << lg) < (int64_t(1) << 18) && (4 << lg) <= layers) ++lg;
+    hipLaunchKernelGGL(k_finalize<T>, dim3(blocks_for(n << lg, 256, INT32_MAX), static_cast<unsigned>(rows)), dim3(256),
+                       0, st, reinterpret_cast<const double2 *>(acc), n, perm, static_cast<cplx<T> *>(out), real_only,
+                       reinterpret_cast<const double2 *>(slab), layer0, layers, tgt_layers, lg);
     return hipGetLastError();
 }
 
@@ -1519,12 +1601,8 @@ template hipError_t launch_interp<float>(const PairDev *, const int64_t *, int, 
 template hipError_t launch_interp<double>(const PairDev *, const int64_t *, int, int64_t, const double *, int64_t,
                                           const double *, const void *, int64_t, double *, int64_t, int, int, double,
                                           double, int, hipStream_t);
-template hipError_t launch_direct<float>(const DirectItem *, int64_t, const double *, int64_t, const double *, int64_t,
-                                         const int32_t *, const void *, int64_t, double *, int64_t, int, double, int,
-                                         int, int, int64_t, const void *, hipStream_t);
-template hipError_t launch_direct<double>(const DirectItem *, int64_t, const double *, int64_t, const double *, int64_t,
-                                          const int32_t *, const void *, int64_t, double *, int64_t, int, double, int,
-                                          int, int, int64_t, const void *, hipStream_t);
+template hipError_t launch_direct<float>(const DirectLaunch &, hipStream_t);
+template hipError_t launch_direct<double>(const DirectLaunch &, hipStream_t);
 template <typename T>
 hipError_t launch_dde_scale(const void *w, const void *x, void *out, int64_t n, int terms, int conj_w, hipStream_t st)
 {
@@ -1551,7 +1629,9 @@ template hipError_t launch_dde_scale<double>(const void *, const void *, void *,
 template hipError_t launch_dde_combine<float>(const void *, const void *, void *, int64_t, int, int, int, hipStream_t);
 template hipError_t launch_dde_combine<double>(const void *, const void *, void *, int64_t, int, int, int,
                                                hipStream_t);
-template hipError_t launch_finalize<float>(const double *, int64_t, const int32_t *, void *, int, hipStream_t);
-template hipError_t launch_finalize<double>(const double *, int64_t, const int32_t *, void *, int, hipStream_t);
+template hipError_t launch_finalize<float>(const double *, int64_t, const int32_t *, void *, int, const double *, int, int,
+                                             const int32_t *, int, hipStream_t);
+template hipError_t launch_finalize<double>(const double *, int64_t, const int32_t *, void *, int, const double *, int, int,
+                                             const int32_t *, int, hipStream_t);
 
 }  // namespace hvox

@@ -623,33 +623,57 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
     // source-segment-major: consecutive workgroups (spread over the XCDs) work on
     // the same source segment for different target tiles, so a segment is
     // fetched into each XCD's L2 once rather than once per tile.
-    int64_t seg = kDirectSeg;
-    for (; seg > 2 * kDirectSrcTile; seg /= 2) {
+    // Where even the shortest segments leave most CUs without work, tiles of
+    // kDirectNarrow targets whose wavefronts divide the sources take over
+    // (2,000 x 3,072 points: 24 wide items of 37 us; narrow: 384 items of 5 us).
+    auto items_of = [&](int64_t tile, int64_t len) {
         int64_t items = 0;
         for (const Group &g : groups) {
             int64_t segs = 0;
-            for (const auto &r : g.ranges) segs += (r.second - r.first + seg - 1) / seg;
-            items += segs * ((g.t1 - g.t0 + kDirectTile - 1) / kDirectTile);
+            for (const auto &r : g.ranges) segs += (r.second - r.first + len - 1) / len;
+            items += segs * ((g.t1 - g.t0 + tile - 1) / tile);
         }
-        if (items >= kDirectMinItems) break;
+        return items;
+    };
+    int64_t seg = kDirectSeg, min_seg = 2 * kDirectSrcTile;
+    dp->direct_tile = kDirectTile;
+    if (items_of(kDirectTile, min_seg) < kDirectFewItems) {
+        dp->direct_tile = kDirectNarrow;
+        min_seg = kDirectNarrowSeg;
     }
-    // layer of an item: its source segment's position in its group's list (deterministic plans
-    // launch layer by layer; other plans launch every item at once)
+    while (seg > min_seg && items_of(dp->direct_tile, seg) < (dp->direct_tile == kDirectTile ? kDirectMinItems : kDirectFewItems))
+        seg /= 2;
+    // layer of an item: its source segment's position in its group's list
     std::vector<int64_t> layer_of;
+    dp->layers = 0;
+    dp->tgt_layers.assign(static_cast<size_t>(tgt.n), 0);
     for (const Group &g : groups) {
         int64_t layer = 0;
         for (const auto &r : g.ranges)
             for (int64_t s0 = r.first; s0 < r.second; s0 += seg, ++layer)
-                for (int64_t t0 = g.t0; t0 < g.t1; t0 += kDirectTile) {
+                for (int64_t t0 = g.t0; t0 < g.t1; t0 += dp->direct_tile) {
                     DirectItem it;
                     it.tgt_off = t0;
                     it.src_off = s0;
-                    it.tgt_cnt = static_cast<int32_t>(std::min<int64_t>(kDirectTile, g.t1 - t0));
-                    it.src_cnt = static_cast<int32_t>(std::min<int64_t>(seg, r.second - s0));
+                    it.layer = static_cast<int32_t>(layer);
+                    it.tgt_cnt = static_cast<int16_t>(std::min<int64_t>(dp->direct_tile, g.t1 - t0));
+                    it.src_cnt = static_cast<int16_t>(std::min<int64_t>(seg, r.second - s0));
                     dp->direct.push_back(it);
                     layer_of.push_back(layer);
                 }
+        dp->layers = std::max(dp->layers, layer);
+        std::fill(dp->tgt_layers.begin() + g.t0, dp->tgt_layers.begin() + g.t1, static_cast<int32_t>(layer));
     }
+    // Stored sums: a small direction without NUFFT sub-problems (no accumulator to clear, no
+    // atomics), and deterministic plans, whose layers would otherwise be launches of
+    // one item per target tile each (70,001 x 90,007 points: 35 launches of 176 workgroups).
+    dp->slab_layers = 0;
+    if (!dp->direct.empty()) {
+        if (p.deterministic()) dp->slab_layers = std::min(dp->layers, kSlabElemsDet / std::max<int64_t>(tgt.n, 1));
+        else if (nufft.empty() && dp->layers * tgt.n <= kSlabElems) dp->slab_layers = dp->layers;
+        if (dp->slab_layers < std::min<int64_t>(2, dp->layers)) dp->slab_layers = 0;
+    }
+    if (dp->slab_layers == 0) dp->tgt_layers.clear();
     dp->direct_layer_off.assign(1, 0);
     if (p.deterministic() && !dp->direct.empty()) {
         const int64_t nl = *std::max_element(layer_of.begin(), layer_of.end()) + 1;
@@ -834,6 +858,7 @@ int64_t device_bytes_bound(const HostPlan &hp)
     const int64_t staged = p.dtype == HVOX_F64 ? sizeof(StagedSrc<double>) : sizeof(StagedSrc<float>);
     int64_t b = 24 * (nv + np) + 4 * (nv + np) + 8 * (nv + np) + 4 * (nv + np);   // coords, perms, deconv, chunk ids
     b += 16 * static_cast<int64_t>(kRowBatch) * std::max(nv, np);                // accumulator
+    b += 16 * hp.slab_elems;                                                     // direct sums stored per layer
     b += prec * static_cast<int64_t>(hp.precor_nu.size()) + delta * hp.tw_total;
     if (p.dtype == HVOX_F64) b += 16 * kCisTab;                                 // direct-sum phase table
     const int nq = 2 * std::max(p.w, p.w2) + 60;
@@ -844,7 +869,7 @@ int64_t device_bytes_bound(const HostPlan &hp)
     int64_t max_pts = 0, temp = 0;
     for (const DirPlan *dp : {&hp.syn, &hp.ana}) {
         b += static_cast<int64_t>(dp->pairs.size() * sizeof(PairDev));
-        b += static_cast<int64_t>(dp->direct.size() * sizeof(DirectItem));
+        b += static_cast<int64_t>(dp->direct.size() * sizeof(DirectItem) + dp->tgt_layers.size() * sizeof(int32_t));
         b += 8 * static_cast<int64_t>(dp->pre_pts.size() + dp->pre_tgts.size() + dp->pre_ttiles.size() +
                                       dp->pre_tiles[0].size() + dp->pre_tiles[1].size() + dp->pre_tiles[2].size());
         int64_t pts = 0;
@@ -1027,6 +1052,7 @@ int make_host_plan(const double *uvw, int64_t n_vis, const double *xyz, int64_t 
     hp->ws_row = hp->rows > 1 ? (used + 63) / 64 * 64 : used;
     hp->ws_elems = hp->ws_row * hp->rows;
     hp->max_pts = max_pts;
+    hp->slab_elems = hp->rows * std::max(hp->syn.slab_layers * n_vis, hp->ana.slab_layers * n_pix);
 
     hp->tw_len.clear();
     hp->tw_off.clear();
