@@ -37,7 +37,12 @@ constexpr int kDirectTile = 512;     // targets per direct-sum workgroup (two pe
 constexpr int kDirectNarrow = 128;   // the same where wide tiles leave the GPU idle: the wavefronts divide the sources
 constexpr int kDirectSrcTile = 256;  // sources staged in LDS at a time
 constexpr int kDirectSeg = 8192;     // longest source segment of a direct-sum work item
-constexpr int64_t kDirectMinItems = 4096;   // shorter segments while a plan has fewer direct work items
+// shorter segments while a plan has fewer direct work items: about ten rounds of the
+// workgroups that the GPU holds (four or five per CU), of which the last is partly
+// empty (138,750 x 150,000 points, float64: 5,149 items in five rounds and a bit, 14.1 ms;
+// 16,384 items: 13.2 ms)
+constexpr int64_t kDirectMinItems = 16384;
+constexpr int64_t kDirectMinItemsDet = 4096;   // deterministic plans: more items are more stored sums or launches
 // a direction whose wide tiles give fewer items than this (four per CU) at the shortest
 // wide segment takes narrow tiles and segments down to kDirectNarrowSeg
 constexpr int64_t kDirectFewItems = 1024;

@@ -641,26 +641,31 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
         dp->direct_tile = kDirectNarrow;
         min_seg = kDirectNarrowSeg;
     }
-    while (seg > min_seg && items_of(dp->direct_tile, seg) < (dp->direct_tile == kDirectTile ? kDirectMinItems : kDirectFewItems))
-        seg /= 2;
+    const int64_t enough = dp->direct_tile == kDirectNarrow ? kDirectFewItems
+                                                            : (p.deterministic() ? kDirectMinItemsDet : kDirectMinItems);
+    while (seg > min_seg && items_of(dp->direct_tile, seg) < enough) seg /= 2;
     // layer of an item: its source segment's position in its group's list
     std::vector<int64_t> layer_of;
     dp->layers = 0;
     dp->tgt_layers.assign(static_cast<size_t>(tgt.n), 0);
     for (const Group &g : groups) {
         int64_t layer = 0;
-        for (const auto &r : g.ranges)
-            for (int64_t s0 = r.first; s0 < r.second; s0 += seg, ++layer)
+        for (const auto &r : g.ranges) {
+            // equal segments, whole staged tiles
+            const int64_t len = r.second - r.first, n = (len + seg - 1) / seg, unit = std::min<int64_t>(seg, kDirectSrcTile);
+            const int64_t cut = ((len + n - 1) / n + unit - 1) / unit * unit;
+            for (int64_t s0 = r.first; s0 < r.second; s0 += cut, ++layer)
                 for (int64_t t0 = g.t0; t0 < g.t1; t0 += dp->direct_tile) {
                     DirectItem it;
                     it.tgt_off = t0;
                     it.src_off = s0;
                     it.layer = static_cast<int32_t>(layer);
                     it.tgt_cnt = static_cast<int16_t>(std::min<int64_t>(dp->direct_tile, g.t1 - t0));
-                    it.src_cnt = static_cast<int16_t>(std::min<int64_t>(seg, r.second - s0));
+                    it.src_cnt = static_cast<int16_t>(std::min<int64_t>(cut, r.second - s0));
                     dp->direct.push_back(it);
                     layer_of.push_back(layer);
                 }
+        }
         dp->layers = std::max(dp->layers, layer);
         std::fill(dp->tgt_layers.begin() + g.t0, dp->tgt_layers.begin() + g.t1, static_cast<int32_t>(layer));
     }
