@@ -30,6 +30,21 @@ int hvox_test_fft(int32_t dtype, int32_t n, int32_t nin, int32_t nlines, int32_t
                   int32_t sign, const void *in, void *out, void *stream);
 
 /*
+ * The two-factor x and y passes (the FFT step of HVOX Sect. 3 for lengths that
+ * split into two factors of the kernel's list) on a grid in[nz][n1y][n1x]:
+ *   out[z][p][q] = sum_{a < n1y, b < n1x} in[z][a][b]
+ *                  exp(sign 2 pi i ((b - n1x/2) (wsx + p) / nx + (a - n1y/2) (wsy + q) / ny)),
+ *   p < wx, q < wy.
+ * axis: host array of 4 values each for x and y: length n (at most 1600 in HVOX_F32, 648
+ * in HVOX_F64), input size n1 (even, at most n; x: at most 1024), first kept output and
+ * number of kept outputs: either 0 and n, or -R and 2 R + 1 < n.  in and out:
+ * device buffers of the dtype's complex values.  HVOX_ERR_ARG for a length without two
+ * factors.  The call returns after synchronising the stream.
+ */
+int hvox_test_fft_two(int32_t dtype, const int32_t axis[8], int32_t nz, int32_t sign, const void *in, void *out,
+                      void *stream);
+
+/*
  * The radix plan of the FFT passes for lines of n points (the stages of the
  * FFT step of HVOX Sect. 3): writes the radix of every Stockham stage, first
  * stage first, to radix[0 .. k-1] and returns k (at most 16), or a negative

@@ -30,10 +30,13 @@ hipError_t launch_prephase(const PairDev *, const int64_t *, int, int64_t, const
                            const void *, int64_t, int, void *, void *, int64_t, double, int, hipStream_t);
 template <typename T>
 hipError_t launch_spread(const PairDev *, const SpreadTile *, int64_t, const int32_t *, const void *, const void *,
-                         int64_t, int, void *, int64_t, int, double, hipStream_t);
+                         int64_t, int, void *, int64_t, const void *, int, double, hipStream_t);
 template <typename T>
-hipError_t launch_fft(const PairDev *, const int64_t *, int, int64_t, int, void *, const void *, const void *,
-                      const uint32_t *, int, int, double, int, int64_t, hipStream_t);
+hipError_t launch_fft(const PairDev *, const int64_t *, int, int64_t, int, void *, const void *, const uint32_t *, int,
+                      int, double, int, int64_t, hipStream_t);
+template <typename T>
+hipError_t launch_fft_two(const PairDev *, const int64_t *, int, int64_t, int, void *, const void *, const uint32_t *,
+                          int, int, double, int, int64_t, hipStream_t);
 template <typename T>
 hipError_t launch_transpose(const PairDev *, const int64_t *, int, int64_t, void *, int, int64_t, hipStream_t);
 template <typename T>
@@ -196,6 +199,13 @@ std::vector<double> soa(const std::vector<double> &aos, const std::vector<int32_
     return out;
 }
 
+// exponent of entry j of an n-point twiddle table: j, or (two-factor passes with A = rows)
+// k b of the entry for row k of A and column b of B = n / A
+int32_t twiddle_exponent(int32_t j, int32_t n, int32_t rows)
+{
+    return rows ? (j / (n / rows)) * (j % (n / rows)) : j;
+}
+
 std::vector<int32_t> chunk_of_order(const ChunkSet &cs)
 {
     std::vector<int32_t> out(cs.n);
@@ -352,21 +362,25 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
                 }));
                 HVOX_TRY(timed(pl, may_time, HVOX_K_SPREAD, st, [&] {
                     return launch_spread<T>(pairs, dd.spread_tiles + b.list_off, b.list_cnt, dd.records, sc.stage,
-                                            sc.xval, hp.max_pts, nr, sc.ws, hp.ws_row, p.w, p.beta, st);
+                                            sc.xval, hp.max_pts, nr, sc.ws, hp.ws_row, pl->precor, p.w, p.beta, st);
                 }));
                 const int64_t n_add = dd.spread_add_cnt[&b - dp.batches.data()];
                 if (n_add > 0)
                     HVOX_TRY(timed(pl, may_time, HVOX_K_SPREAD, st, [&] {
                         return launch_spread<T>(pairs, dd.spread_tiles + b.list_off + b.list_cnt, n_add, dd.records,
-                                                sc.stage, sc.xval, hp.max_pts, nr, sc.ws, hp.ws_row, p.w, p.beta, st);
+                                                sc.stage, sc.xval, hp.max_pts, nr, sc.ws, hp.ws_row, pl->precor, p.w, p.beta, st);
                     }));
                 for (int pass = 0; pass < 3; ++pass) {
                     HVOX_TRY(timed(pl, may_time, HVOX_K_FFT_X + pass, st, [&] {
+                        if (b.two && pass < 2)
+                            return launch_fft_two<T>(pairs, dd.pre_tiles[pass] + b.pre_tiles[pass], np, b.tiles[pass],
+                                                     pass, sc.ws, pl->tw, dd.occ, b.two_lds[pass],
+                                                     b.two_threads[pass], iota, nr, hp.ws_row, st);
                         return launch_fft<T>(pairs, dd.pre_tiles[pass] + b.pre_tiles[pass], np, b.tiles[pass], pass,
-                                             sc.ws, pl->tw, pl->precor, dd.occ, b.lds_elems[pass],
+                                             sc.ws, pl->tw, dd.occ, b.lds_elems[pass],
                                              b.max_pass_len[pass], iota, nr, hp.ws_row, st);
                     }));
-                    if (pass == 0)
+                    if (pass == 0 && !b.two)
                         HVOX_TRY(timed(pl, may_time, HVOX_K_TRANSPOSE, st, [&] {
                             return launch_transpose<T>(pairs, dd.pre_ttiles + b.pre_ttiles, np, b.ttiles, sc.ws, nr,
                                                        hp.ws_row, st);
@@ -731,7 +745,7 @@ int build_device(hvox_plan_s *pl, hipStream_t st, std::string *err)
         tw64.resize(hp.tw_total);
         for (size_t t = 0; t < hp.tw_len.size(); ++t)
             for (int32_t j = 0; j < hp.tw_len[t]; ++j) {
-                double a = 2.0 * M_PI * j / hp.tw_len[t];
+                const double a = 2.0 * M_PI * twiddle_exponent(j, hp.tw_len[t], hp.tw_rows[t]) / hp.tw_len[t];
                 tw64[hp.tw_off[t] + j] = make_double2(std::cos(a), -std::sin(a));
             }
         double2 *d = nullptr;
@@ -750,7 +764,7 @@ int build_device(hvox_plan_s *pl, hipStream_t st, std::string *err)
         tw32.resize(hp.tw_total);
         for (size_t t = 0; t < hp.tw_len.size(); ++t)
             for (int32_t j = 0; j < hp.tw_len[t]; ++j) {
-                double a = 2.0 * M_PI * j / hp.tw_len[t];
+                const double a = 2.0 * M_PI * twiddle_exponent(j, hp.tw_len[t], hp.tw_rows[t]) / hp.tw_len[t];
                 tw32[hp.tw_off[t] + j] = make_float2(static_cast<float>(std::cos(a)), static_cast<float>(-std::sin(a)));
             }
         float2 *d = nullptr;
@@ -1257,7 +1271,7 @@ extern "C" int hvox_test_fft(int32_t dtype, int32_t n, int32_t nin, int32_t nlin
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t delta = dtype == HVOX_F64 ? 16 : 8;
     // one sub-problem whose x pass is exactly this transform: grid 1 is
-    // [1][nlines][nin], pre-correction 1, output window along x only
+    // [1][nlines][nin], output window along x only
     PairDev pd{};
     pd.n1[0] = nin; pd.n1[1] = nlines; pd.n1[2] = 1;
     pd.n2[0] = n; pd.n2[1] = nlines; pd.n2[2] = 1;
@@ -1271,10 +1285,7 @@ extern "C" int hvox_test_fft(int32_t dtype, int32_t n, int32_t nin, int32_t nlin
     pd.bufG = 0;
     pd.bufA = gin;
     pd.bufB = gin;
-    pd.precor[0] = 0; pd.precor[1] = nin; pd.precor[2] = nin + nlines;
     pd.tw[0] = 0;
-    std::vector<double> ones(nin + nlines + 1, 1.0);
-    std::vector<float> ones32(nin + nlines + 1, 1.0f);
     std::vector<double2> tw64(n);
     std::vector<float2> tw32(n);
     for (int j = 0; j < n; ++j) {
@@ -1283,35 +1294,99 @@ extern "C" int hvox_test_fft(int32_t dtype, int32_t n, int32_t nin, int32_t nlin
         tw32[j] = make_float2(static_cast<float>(std::cos(a)), static_cast<float>(-std::sin(a)));
     }
     std::vector<int64_t> prefix = {0, tiles};
-    void *d_ws = nullptr, *d_tw = nullptr, *d_pd = nullptr, *d_pre = nullptr, *d_one = nullptr;
+    void *d_ws = nullptr, *d_tw = nullptr, *d_pd = nullptr, *d_pre = nullptr;
     auto cleanup = [&]() {
-        for (void *p : {d_ws, d_tw, d_pd, d_pre, d_one}) if (p) (void)hipFree(p);
+        for (void *p : {d_ws, d_tw, d_pd, d_pre}) if (p) (void)hipFree(p);
     };
     hipError_t e = hipMalloc(&d_ws, delta * (gin + gout));
     if (e == hipSuccess) e = hipMalloc(&d_tw, delta * n);
     if (e == hipSuccess) e = hipMalloc(&d_pd, sizeof(PairDev));
     if (e == hipSuccess) e = hipMalloc(&d_pre, sizeof(int64_t) * 2);
-    if (e == hipSuccess) e = hipMalloc(&d_one, delta / 2 * ones.size());
     if (e == hipSuccess) e = hipMemcpyAsync(d_ws, in, delta * gin, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_tw, dtype == HVOX_F64 ? static_cast<const void *>(tw64.data()) : tw32.data(), delta * n,
                            hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(d_pd, &pd, sizeof(PairDev), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(d_pre, prefix.data(), sizeof(int64_t) * 2, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(d_one, dtype == HVOX_F64 ? static_cast<const void *>(ones.data()) : ones32.data(),
-                           delta / 2 * ones.size(), hipMemcpyHostToDevice, st);
     const int lds = fft_lds_elems(pd.lines_per_tile[0], n);
     if (e == hipSuccess)
         e = dtype == HVOX_F64
                 ? launch_fft<double>(static_cast<PairDev *>(d_pd), static_cast<int64_t *>(d_pre), 1, tiles, 0, d_ws,
-                                     d_tw, d_one, nullptr, lds, n, sign, 1, 0, st)
+                                     d_tw, nullptr, lds, n, sign, 1, 0, st)
                 : launch_fft<float>(static_cast<PairDev *>(d_pd), static_cast<int64_t *>(d_pre), 1, tiles, 0, d_ws,
-                                    d_tw, d_one, nullptr, lds, n, sign, 1, 0, st);
+                                    d_tw, nullptr, lds, n, sign, 1, 0, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(out, static_cast<char *>(d_ws) + delta * gin, delta * gout, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     cleanup();
+    if (e != hipSuccess) return fail(HVOX_ERR_HIP, std::string("HIP: ") + hipGetErrorString(e));
+    return HVOX_OK;
+}
+
+extern "C" int hvox_test_fft_two(int32_t dtype, const int32_t axis[8], int32_t nz, int32_t sign, const void *in,
+                                 void *out, void *stream)
+{
+    using namespace hvox;
+    if ((dtype != HVOX_F32 && dtype != HVOX_F64) || !axis || nz < 1 || (sign != 1 && sign != -1) || !in || !out)
+        return fail(HVOX_ERR_ARG, "bad FFT test arguments");
+    PairDev pd{};
+    pd.n1[2] = nz; pd.n2[2] = 2; pd.wcount[2] = 1;
+    int threads[2], lds[2];
+    int64_t tiles[2], prefix[4] = {0, 0, 0, 0};
+    for (int d = 0; d < 2; ++d) {
+        const int32_t n = axis[4 * d], n1 = axis[4 * d + 1], ws = axis[4 * d + 2], wc = axis[4 * d + 3];
+        const bool window = (ws == 0 && wc == n) || (ws < 0 && wc == 1 - 2 * ws && wc < n);
+        if (n < 2 || n > kFftMaxLen || !factor_two(n, dtype, pd.two[d]) || n1 < 2 || (n1 & 1) || n1 > n || !window ||
+            (d == 0 && n1 > kFft2MaxX))
+            return fail(HVOX_ERR_ARG, "bad axis of a two-factor FFT");
+        pd.n1[d] = n1; pd.n2[d] = n; pd.wstart[d] = ws; pd.wcount[d] = wc;
+        pd.tw[d] = d ? axis[0] : 0;
+    }
+    const int64_t cols = kFft2Block * fft2_blocks(pd.wcount[0]);
+    for (int d = 0; d < 2; ++d) {
+        const int a = pd.two[d][0], b = pd.two[d][1], lines = fft2_lines(a, b, dtype);
+        threads[d] = (lines * a + 63) / 64 * 64;
+        lds[d] = lines * fft2_line(a, b);
+        tiles[d] = ((d ? cols : pd.n1[1]) * nz + lines - 1) / lines;
+        prefix[2 * d + 1] = tiles[d];
+    }
+    const int64_t gin = static_cast<int64_t>(pd.n1[0]) * pd.n1[1] * nz, mid = cols * pd.n1[1] * nz;
+    const int64_t gout = static_cast<int64_t>(pd.wcount[0]) * pd.wcount[1] * nz;
+    pd.bufG = 0;
+    pd.bufA = gin;
+    pd.bufB = gin + mid;
+    std::vector<double2> tw64;
+    std::vector<float2> tw32;
+    for (int d = 0; d < 2; ++d)
+        for (int j = 0; j < pd.n2[d]; ++j) {
+            const double t = 2.0 * M_PI * twiddle_exponent(j, pd.n2[d], pd.two[d][0]) / pd.n2[d];
+            tw64.push_back(make_double2(std::cos(t), -std::sin(t)));
+            tw32.push_back(make_float2(static_cast<float>(std::cos(t)), static_cast<float>(-std::sin(t))));
+        }
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const size_t delta = dtype == HVOX_F64 ? 16 : 8;
+    void *d_ws = nullptr, *d_tw = nullptr, *d_pd = nullptr, *d_pre = nullptr;
+    hipError_t e = hipMalloc(&d_ws, delta * (gin + mid + gout));
+    if (e == hipSuccess) e = hipMalloc(&d_tw, delta * tw64.size());
+    if (e == hipSuccess) e = hipMalloc(&d_pd, sizeof(PairDev));
+    if (e == hipSuccess) e = hipMalloc(&d_pre, sizeof(prefix));
+    if (e == hipSuccess) e = hipMemcpyAsync(d_ws, in, delta * gin, hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(d_tw, dtype == HVOX_F64 ? static_cast<const void *>(tw64.data()) : tw32.data(),
+                           delta * tw64.size(), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_pd, &pd, sizeof(PairDev), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_pre, prefix, sizeof(prefix), hipMemcpyHostToDevice, st);
+    for (int d = 0; d < 2 && e == hipSuccess; ++d) {
+        const auto *pre = static_cast<int64_t *>(d_pre) + 2 * d;
+        e = dtype == HVOX_F64 ? launch_fft_two<double>(static_cast<PairDev *>(d_pd), pre, 1, tiles[d], d, d_ws, d_tw,
+                                                       nullptr, lds[d], threads[d], sign, 1, 0, st)
+                              : launch_fft_two<float>(static_cast<PairDev *>(d_pd), pre, 1, tiles[d], d, d_ws, d_tw,
+                                                      nullptr, lds[d], threads[d], sign, 1, 0, st);
+    }
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(out, static_cast<char *>(d_ws) + delta * (gin + mid), delta * gout, hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    for (void *p : {d_ws, d_tw, d_pd, d_pre}) if (p) (void)hipFree(p);
     if (e != hipSuccess) return fail(HVOX_ERR_HIP, std::string("HIP: ") + hipGetErrorString(e));
     return HVOX_OK;
 }

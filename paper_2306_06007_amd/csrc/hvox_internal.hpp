@@ -32,6 +32,25 @@ constexpr int fft_lines(int n)
 // every lane of an access to one or two banks
 constexpr int fft_lds_stride(int n) { return n + 1; }
 constexpr int fft_lds_elems(int lines, int n) { return lines * fft_lds_stride(n); }
+// Two-factor x and y passes (n = A B: an A-point DFT in registers, one exchange
+// through LDS, a B-point DFT in registers): the longest factor per precision, the LDS
+// of a line (A rows of B values; rows an odd number of values apart and lines 8
+// modulo 32, so that neither lanes along a line nor lanes across four lines meet
+// on a bank), and the lines per workgroup: as many fours (kFft2Block, see PairDev) as
+// 256 threads and 40 KB of LDS hold, so that several workgroups share a CU.
+constexpr int kFft2Threads = 256, kFft2Block = 4;
+constexpr int kFft2MaxX = 1024;      // longest grid-1 line (the occupancy bits of its tiles fit 32 bits)
+constexpr int fft2_max_factor(int dtype) { return dtype == HVOX_F64 ? 27 : 40; }
+constexpr int fft2_row(int b) { return b | 1; }
+constexpr int fft2_line(int a, int b) { return (a * fft2_row(b) + 23) / 32 * 32 + 8; }
+constexpr int fft2_lines(int a, int b, int dtype)
+{
+    const int by_threads = kFft2Threads / (kFft2Block * a);
+    const int by_lds = (dtype == HVOX_F64 ? 2560 : 5120) / (kFft2Block * a * b);
+    const int m = by_threads < by_lds ? by_threads : by_lds;
+    return kFft2Block * (m > 1 ? m : 1);
+}
+constexpr int64_t fft2_blocks(int64_t wx) { return (wx + kFft2Block - 1) / kFft2Block; }
 constexpr int kDirectThreads = 256;  // threads of a direct-sum workgroup
 constexpr int kDirectTile = 512;     // targets per direct-sum workgroup (two per thread)
 constexpr int kDirectNarrow = 128;   // the same where wide tiles leave the GPU idle: the wavefronts divide the sources
@@ -89,9 +108,10 @@ static_assert(sizeof(StagedSrc<float>) == 32 && sizeof(StagedSrc<double>) == 64,
 
 // ---- one type-3 sub-problem (source chunk -> target chunk) on the device ---
 // FFT passes: x reads grid 1 (contiguous lines) and writes its kept window
-// line-major; a tiled transpose makes the y lines contiguous; y writes
-// line-major; z reads its (short) lines strided, consecutive lines in
-// adjacent lanes, and writes line-major, leaving a z-fastest grid.
+// line-major; y reads blocks of four lines side by side (two-factor passes) or,
+// after a tiled transpose, contiguous lines, and writes line-major; z reads its (short)
+// lines strided, consecutive lines in adjacent lanes, and writes line-major,
+// leaving a z-fastest grid.
 // Sub-problem math (Sect. 3, the four type-3 steps; centring as in the
 // published type-3 method the paper builds on):
 //   f_k = e^{2 pi i iota s_k.x_c} sum_n [c_n e^{2 pi i iota s_c.x'_n}] e^{2 pi i iota s'_k.x'_n}
@@ -111,15 +131,16 @@ struct PairDev {
     int32_t wstart[3];           // first kept FFT output index (may be negative: periodic)
     int32_t wcount[3];           // kept FFT outputs per dimension
     int32_t nrad[3];             // radix stages per dimension
-    int32_t lines_per_tile[3];   // FFT lines per workgroup, per pass
+    int32_t lines_per_tile[3];   // FFT lines per workgroup, per pass (general passes)
     int64_t bufG, bufA, bufB;    // complex-element offsets of the grid buffers in the workspace:
                                  //   G: grid 1 [n1z][n1y][n1x] (spread output, x-pass input)
-                                 //   A: x-pass output transposed [n1z][wx][n1y] -> z-pass output
-                                 //      [wx][wy][wz] (read by the interpolation)
-                                 //   B: x-pass output [n1z][n1y][wx] -> y-pass output [n1z][wx][wy]
+                                 //   A: x-pass output in blocks of four columns [n1z][wx / 4][n1y][4] (two-factor
+                                 //      passes) or its transpose [n1z][wx][n1y] -> z-pass output [wx][wy][wz]
+                                 //      (read by the interpolation)
+                                 //   B: x-pass output [n1z][n1y][wx] (to be transposed) -> y-pass output [n1z][wx][wy]
     int64_t tile0;               // index of the pair's first grid-1 tile among the direction's tiles
     int32_t ntile[3];            // grid-1 tiles per dimension
-    int32_t pad_;
+    uint8_t two[2][2];           // factors A, B of the x and y passes in two-factor batches
     int64_t precor[3];           // offsets into the pre-correction table (n1[d] entries each)
     int64_t tw[3];               // offsets into the twiddle table (n2[d] entries each)
     uint8_t radix[3][kMaxStages];
@@ -202,6 +223,9 @@ struct Batch {
     int64_t ws_end = 0;                  // end of the batch's workspace use (complex elements)
     int64_t pre_pts = 0, pre_tgts = 0;   // offsets into the prefix arrays (pre_tgts: interp workgroups)
     int64_t pre_tiles[3] = {0, 0, 0};
+    bool two = false;                    // x and y passes in two factors, no transpose
+    int32_t two_threads[2] = {0, 0};     // their workgroup sizes and LDS (complex elements)
+    int32_t two_lds[2] = {0, 0};
     int32_t lds_elems[3] = {0, 0, 0};    // largest LDS need per pass (complex elements)
     int32_t max_pass_len[3] = {0, 0, 0};
 };
@@ -281,6 +305,7 @@ struct HostPlan {
     std::vector<double> precor_nu;       // nu = l / n2 of every pre-correction entry
     std::vector<int32_t> tw_len;         // lengths with a twiddle table
     std::vector<int64_t> tw_off;         // offsets (complex elements) of each table
+    std::vector<int32_t> tw_rows;        // factor A of tables in the order of two-factor passes (0: in order)
     int64_t tw_total = 0;
     // deconvolution: per chunk S_eff (target scale) for each direction
     std::vector<double> syn_tgt_scale;   // [n_vis_chunks * 3]: 1 / (2 sigma S_eff) for vis targets
@@ -312,6 +337,7 @@ int64_t device_bytes_bound(const HostPlan &hp);
 // region in 32-bit arithmetic
 constexpr int64_t kMaxRegionElems = (int64_t(1) << 31) - 1;
 int factor_radices(int32_t n, uint8_t *radix);
+bool factor_two(int32_t n, int dtype, uint8_t f[2]);
 void gauss_legendre(int n, std::vector<double> *x, std::vector<double> *w);
 
 }  // namespace hvox

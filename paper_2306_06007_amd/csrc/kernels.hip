@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "hvox_internal.hpp"
 
@@ -266,8 +267,8 @@ __global__ __launch_bounds__(256) void k_spread(const PairDev *__restrict__ pair
                                                 const int32_t *__restrict__ records,
                                                 const StagedSrc<T> *__restrict__ staged,
                                                 const cplx<T> *__restrict__ xval, int64_t xstride,
-                                                cplx<T> *__restrict__ ws, int64_t ws_stride, int w, T beta,
-                                                T two_over_w, float rwk)
+                                                cplx<T> *__restrict__ ws, int64_t ws_stride,
+                                                const T *__restrict__ precor, int w, T beta, T two_over_w, float rwk)
 {
     static_assert(kTileZ == 8, "the z weights of a source are read as 8 values");
     // per staged source: kTileZ z values in the tile's frame, then w x and w y
@@ -339,6 +340,17 @@ __global__ __launch_bounds__(256) void k_spread(const PairDev *__restrict__ pair
     const PairDev &P = pairs[tile.pair];
     const int gx = ox + x, gy = oy + y;
     if (gx < P.n1[0] && gy < P.n1[1]) {
+        // the pre-correction 1/Phi_hat(l/n2) of the inner FFT, separable, on the way out
+        const T fxy = precor[P.precor[0] + gx] * precor[P.precor[1] + gy];
+#pragma unroll
+        for (int z = 0; z < kTileZ; ++z) {
+            const T f = fxy * precor[P.precor[2] + min(oz + z, P.n1[2] - 1)];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                accr[r][z] *= f;
+                acci[r][z] *= f;
+            }
+        }
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             cplx<T> *grid = ws + r * ws_stride + P.bufG;   // row r's copy of the batch workspace
@@ -365,7 +377,7 @@ __global__ __launch_bounds__(256) void k_spread(const PairDev *__restrict__ pair
 }
 
 // ---------------------------------------------------------------------------
-// FFT passes (type-3 step 2: pre-correction + zero-padded FFT on grid 2).
+// FFT passes (type-3 step 2: zero-padded FFT of the pre-corrected modes on grid 2).
 // ---------------------------------------------------------------------------
 // exp(2 pi i k / R) as (cos, sin), evaluated by the compiler: the angle is
 // folded into [0, pi/4] with the quarter-turn and complement symmetries
@@ -484,8 +496,21 @@ __device__ __forceinline__ void dft_small(cplx<T> *u, T s)
         u[6] = csub<T>(e[2], o2);
         u[3] = cadd<T>(e[3], o3);
         u[7] = csub<T>(e[3], o3);
-    } else if constexpr (R == 9) {
-        dft_two_factor<T, 3, 3>(u, s);
+    } else if constexpr (R == 6) { dft_two_factor<T, 3, 2>(u, s);
+    } else if constexpr (R == 9) { dft_two_factor<T, 3, 3>(u, s);
+    } else if constexpr (R == 10) { dft_two_factor<T, 5, 2>(u, s);
+    } else if constexpr (R == 12) { dft_two_factor<T, 4, 3>(u, s);
+    } else if constexpr (R == 15) { dft_two_factor<T, 5, 3>(u, s);
+    } else if constexpr (R == 16) { dft_two_factor<T, 4, 4>(u, s);
+    } else if constexpr (R == 18) { dft_two_factor<T, 9, 2>(u, s);
+    } else if constexpr (R == 20) { dft_two_factor<T, 5, 4>(u, s);
+    } else if constexpr (R == 24) { dft_two_factor<T, 8, 3>(u, s);
+    } else if constexpr (R == 25) { dft_two_factor<T, 5, 5>(u, s);
+    } else if constexpr (R == 27) { dft_two_factor<T, 9, 3>(u, s);
+    } else if constexpr (R == 30) { dft_two_factor<T, 6, 5>(u, s);
+    } else if constexpr (R == 32) { dft_two_factor<T, 8, 4>(u, s);
+    } else if constexpr (R == 36) { dft_two_factor<T, 9, 4>(u, s);
+    } else if constexpr (R == 40) { dft_two_factor<T, 8, 5>(u, s);
     } else {
         static_assert(R == 5, "radix");
         const T c1 = T(0.30901699437494742410), c2 = T(-0.80901699437494742410);
@@ -576,16 +601,14 @@ __device__ __forceinline__ void fft_stage_radix(int R, cplx<T> *lds, int nl, int
 // zero padding of grid 1 into grid 2 is never stored).  The x and y passes
 // read contiguous lines; the z pass reads its lines strided (line j of the
 // plane is element j of every z-slab, so consecutive lines sit in adjacent
-// lanes).  The x pass also applies the separable pre-correction
-// 1/Phi_hat(l/n2) of all three axes (the (y, z) factor once per line) and
-// reads grid-1 tiles that hold no source as zeros.  The second grid
+// lanes).  The x pass reads grid-1 tiles that hold no source as zeros.  The second grid
 // dimension runs over the data rows of the pass.  Output
 // q of the kept window is FFT index (wstart + q) mod n, written line-major:
 // out[line][q].
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_fft_pass(const PairDev *__restrict__ pairs, const int64_t *__restrict__ prefix,
                                                  int npairs, int pass, cplx<T> *__restrict__ ws,
-                                                 const cplx<T> *__restrict__ twtab, const T *__restrict__ precor,
+                                                 const cplx<T> *__restrict__ twtab,
                                                  const uint32_t *__restrict__ occ, int tw_off, T s,
                                                  int64_t ws_stride)
 {
@@ -594,7 +617,6 @@ __global__ __launch_bounds__(NT) void k_fft_pass(const PairDev *__restrict__ pai
     extern __shared__ unsigned char smem_raw[];
     cplx<T> *lds = reinterpret_cast<cplx<T> *>(smem_raw);
     cplx<T> *ltw = lds + tw_off;              // exp(s 2 pi i j/n), j < n, after the lines
-    __shared__ T lfac[kFftMaxLines];
     __shared__ uint32_t lmask[kFftMaxLines][kOccWords];   // x pass: occupancy bits of each line's tile row
     __shared__ int lbit0[kFftMaxLines];
     const int p = (int)find_segment(prefix, npairs, blockIdx.x);
@@ -627,7 +649,6 @@ __global__ __launch_bounds__(NT) void k_fft_pass(const PairDev *__restrict__ pai
         if ((int)threadIdx.x < nl) {
             const int64_t li = line0 + threadIdx.x;
             const int64_t lz = li / P.n1[1], ly = li - lz * P.n1[1];
-            lfac[threadIdx.x] = precor[P.precor[1] + ly] * precor[P.precor[2] + lz];
             // tiles of this line's row: bit rowbit + tx is tile (tx, ly / 8, lz / 8) of the pair;
             // a tile without sources was never written and reads as zeros (no bitmap: all read)
             const int64_t rowbit = P.tile0 + ((lz / kTileZ) * P.ntile[1] + ly / kTileY) * P.ntile[0];
@@ -645,37 +666,29 @@ __global__ __launch_bounds__(NT) void k_fft_pass(const PairDev *__restrict__ pai
     cplx<T> v[EPT];
     if (pass < 2) {
         const cplx<T> *sb = src + line0 * nin;
-        const T *px = precor + P.precor[0] + half_in;
         const float rn = small_rcp(n);
-        T fx[EPT];             // x pre-correction (pass x), applied after all loads are issued
-        int jl[EPT], slot[EPT];
+        int slot[EPT];
 #pragma unroll
         for (int c = 0; c < EPT; ++c) {
             const int e = threadIdx.x + c * NT;
             v[c] = mk<T>(T(0), T(0));
-            fx[c] = T(1);
-            jl[c] = 0;
             slot[c] = 0;
             if (e < ne) {
                 const int j = small_div(e, rn), f = e - __mul24(j, n);
                 const int l = f < half_n ? f : f - n;
-                jl[c] = j;
                 slot[c] = __mul24(j, ls) + f;
                 bool take = l >= -half_in && l < half_in;
                 if (pass == 0 && take) {
                     const int b = lbit0[j] + ((l + half_in) >> 5);
                     take = (lmask[j][b >> 5] >> (b & 31)) & 1u;
                 }
-                if (take) {
-                    v[c] = sb[__mul24(j, nin) + l + half_in];
-                    if (pass == 0) fx[c] = px[l];
-                }
+                if (take) v[c] = sb[__mul24(j, nin) + l + half_in];
             }
         }
 #pragma unroll
         for (int c = 0; c < EPT; ++c) {
             const int e = threadIdx.x + c * NT;
-            if (e < ne) lds[slot[c]] = pass == 0 ? cscale<T>(v[c], fx[c] * lfac[jl[c]]) : v[c];
+            if (e < ne) lds[slot[c]] = v[c];
         }
     } else {
         const cplx<T> *sb = src + line0;
@@ -713,6 +726,172 @@ __global__ __launch_bounds__(NT) void k_fft_pass(const PairDev *__restrict__ pai
         int m = wst + q;
         if (m < 0) m += n;
         out[e] = lds[__mul24(j, ls) + m];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// x and y passes in two factors, n = A B.  Slot f = a B + b of a line, output
+// m = k + A q:  X[k + A q] = sum_b w_B^(b q) [ w_n^(b k) sum_a w_A^(a k) x[a B + b] ].
+// A thread takes column b: it loads its A elements straight into registers
+// (zero padding and empty tiles are not read), transforms them, multiplies by the twiddles (table in the
+// order [k][b]) and leaves them in LDS; a thread then takes row k, transforms its B
+// values and writes its kept outputs straight from registers.
+// Pass x reads contiguous lines and writes its window in blocks of kFft2Block
+// columns, [z][x / 4][y][4]: four lines at a time fill 128-byte segments (float32), and
+// pass y reads four neighbouring lines as one contiguous run.  No transpose.
+//
+// What bounds it: load, transform, exchange and store of a line follow each other,
+// and LDS and registers let only two to three wavefronts per SIMD overlap
+// them: leaving out loads, stores, transforms or twiddles each saved about a fifth.
+// VALU is busy 45% of the time, traffic is 2.1 (x) and 3.3 TB/s (y, float32), 2.7 and 4.2
+// TB/s (float64) of 4.7 for a copy.  Of the general passes it replaces (four or five radix
+// stages of a 1200-point line, each with its index arithmetic, an LDS round
+// trip and two barriers; a transpose between x and y), x + transpose + y took 26.1 ms on
+// the 3 km dense mesh with every sub-problem a NUFFT (float32; now 15.5) and 11.0 ms on
+// the 1 km one (float64; now 5.8).  Tried: several groups of lines per workgroup
+// (8% slower), twiddles staged in LDS (4% slower: another barrier), smaller
+// groups (10% slower), 128 registers (spills; lengths up to 27 x 27 only).  Longer
+// factors than 27 in float64 would take more than 256 registers.
+// ---------------------------------------------------------------------------
+
+// calls f with the compile-time constant equal to r (a factor of the planner's list)
+template <int MAX, typename F> __device__ __forceinline__ void fft2_switch(int r, F &&f)
+{
+#define HVOX_CASE(R) case R: if constexpr (R <= MAX) f(std::integral_constant<int, R>{}); break;
+    switch (r) {
+        HVOX_CASE(4) HVOX_CASE(5) HVOX_CASE(6) HVOX_CASE(8) HVOX_CASE(9) HVOX_CASE(10) HVOX_CASE(12) HVOX_CASE(15)
+        HVOX_CASE(16) HVOX_CASE(18) HVOX_CASE(20) HVOX_CASE(24) HVOX_CASE(25) HVOX_CASE(27) HVOX_CASE(30)
+        HVOX_CASE(32) HVOX_CASE(36) HVOX_CASE(40)
+    default: break;
+    }
+#undef HVOX_CASE
+}
+
+// element at a 32-bit byte offset from a base that is uniform over the workgroup
+template <typename V> __device__ __forceinline__ V &at_bytes(V *base, uint32_t off)
+{
+    using Byte = std::conditional_t<std::is_const_v<V>, const unsigned char, unsigned char>;
+    return *reinterpret_cast<V *>(reinterpret_cast<Byte *>(base) + off);
+}
+
+template <typename T, int PASS, int SIGN>
+__global__ __launch_bounds__(kFft2Threads, sizeof(T) == 8 ? 2 : 3) void k_fft_two(
+    const PairDev *__restrict__ pairs, const int64_t *__restrict__ prefix, int npairs, cplx<T> *__restrict__ ws,
+    const cplx<T> *__restrict__ twtab, const uint32_t *__restrict__ occ, int64_t ws_stride)
+{
+    static_assert(kTileX == 32 && kFft2MaxX <= 32 * kTileX, "a line's tiles fit a word");
+    constexpr T s = T(SIGN);   // (a constant: the quarter turns of the DFTs cost nothing)
+    constexpr int kType = sizeof(T) == 8 ? HVOX_F64 : HVOX_F32, kMax = fft2_max_factor(kType), kC = kFft2Block;
+    constexpr uint32_t kB = sizeof(cplx<T>);
+    extern __shared__ unsigned char smem_raw[];
+    cplx<T> *ex = reinterpret_cast<cplx<T> *>(smem_raw);
+    ws += (int64_t)blockIdx.y * ws_stride;   // data row blockIdx.y: its copy of the batch workspace
+    const int p = (int)find_segment(prefix, npairs, blockIdx.x);
+    const PairDev &P = pairs[p];
+    const int A = P.two[PASS][0], B = P.two[PASS][1], n = P.n2[PASS], half_in = P.n1[PASS] / 2;
+    const int L = fft2_lines(A, B, kType), row = fft2_row(B), ls = fft2_line(A, B);
+    const int wx = P.wcount[0], n1x = P.n1[0], n1y = P.n1[1], n1z = P.n1[2];
+    const int nb = (int)fft2_blocks(wx);          // blocks of columns in a grid plane
+    const int lines = PASS == 0 ? n1z * n1y : n1z * nb * kC;   // (a region holds fewer than 2^31 elements)
+    const int line0 = (int)(blockIdx.x - prefix[p]) * L;
+    const int t = threadIdx.x;
+    {
+        // column b of line j: pass x along the line in adjacent lanes, pass y across the four lines of a block first
+        int j, b;
+        if (PASS == 0) { j = t / B; b = t - j * B; }
+        else { const int g = t / (kC * B), r = t - g * (kC * B); b = r / kC; j = g * kC + (r - b * kC); }
+        const int li = line0 + j;
+        const cplx<T> *src;
+        uint32_t off;                 // byte offset of the line's first cell
+        uint32_t tiles = ~0u;         // occupied tiles of the line's row
+        bool on = j < L && li < lines;
+        if (PASS == 0) {
+            src = ws + P.bufG + (int64_t)line0 * n1x;
+            off = (uint32_t)(j * n1x) * kB;
+            if (on && occ) {   // (padded: the word past a row's last tile may be read)
+                const int lz = li / n1y, ly = li - lz * n1y;
+                const int64_t bit = P.tile0 + ((int64_t)(lz / kTileZ) * P.ntile[1] + ly / kTileY) * P.ntile[0];
+                const uint32_t *o = occ + (bit >> 5);
+                tiles = __builtin_amdgcn_alignbit(o[1], o[0], (uint32_t)(bit & 31));
+            }
+        } else {
+            // line c of block zb / z of plane z (the last block may hold columns past the window)
+            const int zb0 = line0 / kC, zb = li / kC, c = li - zb * kC, z = zb / nb;
+            on = on && (zb - z * nb) * kC + c < wx;
+            src = ws + P.bufA + (int64_t)zb0 * n1y * kC;
+            off = (uint32_t)((zb - zb0) * n1y * kC + c) * kB;
+        }
+        const cplx<T> *tw = twtab + P.tw[PASS];   // order [k][b]
+        // slot f = a B + b holds mode f (f < half_in, cell f + half_in) or mode f - n (f >= n -
+        // half_in, cell f - n + half_in), else zero
+        constexpr uint32_t kStep = PASS == 0 ? kB : kB * kC;
+        const uint32_t front = off + (uint32_t)(b + half_in) * kStep, back = front - (uint32_t)n * kStep;
+        cplx<T> *to = ex + j * ls + b;
+        fft2_switch<kMax>(A, [&](auto RA) {
+            constexpr int R = decltype(RA)::value;
+            cplx<T> v[R];
+#pragma unroll
+            for (int a = 0; a < R; ++a) {
+                const bool lo = b < half_in - a * B, hi = b >= n - half_in - a * B;
+                bool take = on && (lo || hi);
+                if (PASS == 0) {
+                    const int cell = (lo ? half_in : half_in - n) + a * B + b;
+                    take = take && __builtin_amdgcn_ubfe(tiles, cell >> 5, 1);
+                }
+                v[a] = mk<T>(T(0), T(0));
+                if (take) v[a] = at_bytes(src, (lo ? front : back) + (uint32_t)(a * B) * kStep);
+            }
+            dft_small<T, R>(v, s);
+            if (on) {
+                to[0] = v[0];
+#pragma unroll
+                for (int k = 1; k < R; ++k) {
+                    const cplx<T> w = at_bytes(tw, (uint32_t)(k * B + b) * kB);   // exp(-2 pi i k b / n), conjugated for s = +1
+                    to[k * row] = cmul<T>(v[k], mk<T>(w.x, SIGN < 0 ? w.y : -w.y));
+                }
+            }
+        });
+    }
+    __syncthreads();
+    {
+        // row k of line j: pass x across four lines in adjacent lanes (its blocks of columns), pass y along the line
+        int j, k;
+        if (PASS == 0) { const int g = t / (kC * A), r = t - g * (kC * A); k = r / kC; j = g * kC + (r - k * kC); }
+        else { j = t / A; k = t - j * A; }
+        const int li = line0 + j;
+        bool on = j < L && li < lines;
+        // kept window: wstart is 0 (whole line) or -R with 2 R < n
+        const int q0 = k - P.wstart[PASS], wcnt = P.wcount[PASS];
+        cplx<T> *dst;
+        uint32_t off;                 // byte offset of the line's first kept output
+        if (PASS == 0) {
+            const int lz0 = line0 / n1y, lz = li / n1y, ly = li - lz * n1y;
+            dst = ws + P.bufA + (int64_t)lz0 * nb * n1y * kC;
+            off = (uint32_t)((lz - lz0) * nb * n1y + ly) * (kC * kB);
+        } else {
+            const int zb0 = line0 / kC, z0 = zb0 / nb, x0 = (zb0 - z0 * nb) * kC, first = z0 * wx + x0;
+            const int zb = li / kC, z = zb / nb, x = (zb - z * nb) * kC + (li - zb * kC);
+            on = on && x < wx;
+            dst = ws + P.bufB + (int64_t)first * wcnt;
+            off = (uint32_t)((z * wx + x - first) * wcnt) * kB;
+        }
+        const cplx<T> *from = ex + j * ls + k * row;
+        const uint32_t plane = n1y * kC;   // pass x: elements from a block of columns to the next
+        if (on)
+            fft2_switch<kMax>(B, [&](auto RB) {
+                constexpr int R = decltype(RB)::value;
+                cplx<T> u[R];
+#pragma unroll
+                for (int i = 0; i < R; ++i) u[i] = from[i];
+                dft_small<T, R>(u, s);
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    int q = q0 + A * i;
+                    if (q >= wcnt) q -= n;
+                    const uint32_t e = PASS == 0 ? __umul24(q >> 2, plane) + (q & (kC - 1)) : q;
+                    if (q >= 0) at_bytes(dst, off + e * kB) = u[i];
+                }
+            });
     }
 }
 
@@ -1406,26 +1585,26 @@ hipError_t launch_prephase(const PairDev *pairs, const int64_t *pprefix, int npa
 
 template <typename T, int NR>
 static void spread_rows(const PairDev *pairs, const SpreadTile *tiles, int64_t ntiles, const int32_t *records,
-                        const void *stage, const void *xval, int64_t xstride, void *ws, int64_t ws_stride, int w,
-                        double beta, hipStream_t st)
+                        const void *stage, const void *xval, int64_t xstride, void *ws, int64_t ws_stride,
+                        const void *precor, int w, double beta, hipStream_t st)
 {
     hipLaunchKernelGGL((k_spread<T, NR>), dim3(static_cast<unsigned>(ntiles)), dim3(256), 0, st, pairs, tiles, records,
                        static_cast<const StagedSrc<T> *>(stage), static_cast<const cplx<T> *>(xval), xstride,
-                       static_cast<cplx<T> *>(ws), ws_stride, w, T(beta), T(2.0 / w),
+                       static_cast<cplx<T> *>(ws), ws_stride, static_cast<const T *>(precor), w, T(beta), T(2.0 / w),
                        1.0f / static_cast<float>(2 * w + kTileZ));
 }
 
 template <typename T>
 hipError_t launch_spread(const PairDev *pairs, const SpreadTile *tiles, int64_t ntiles, const int32_t *records,
                          const void *stage, const void *xval, int64_t xstride, int rows, void *ws, int64_t ws_stride,
-                         int w, double beta, hipStream_t st)
+                         const void *precor, int w, double beta, hipStream_t st)
 {
     if (ntiles <= 0) return hipSuccess;
     switch (rows) {
-    case 1: spread_rows<T, 1>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, w, beta, st); break;
-    case 2: spread_rows<T, 2>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, w, beta, st); break;
-    case 3: spread_rows<T, 3>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, w, beta, st); break;
-    case 4: spread_rows<T, 4>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, w, beta, st); break;
+    case 1: spread_rows<T, 1>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, precor, w, beta, st); break;
+    case 2: spread_rows<T, 2>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, precor, w, beta, st); break;
+    case 3: spread_rows<T, 3>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, precor, w, beta, st); break;
+    case 4: spread_rows<T, 4>(pairs, tiles, ntiles, records, stage, xval, xstride, ws, ws_stride, precor, w, beta, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1433,25 +1612,41 @@ hipError_t launch_spread(const PairDev *pairs, const SpreadTile *tiles, int64_t 
 
 template <typename T>
 hipError_t launch_fft(const PairDev *pairs, const int64_t *prefix, int npairs, int64_t tiles, int pass, void *ws,
-                      const void *tw, const void *precor, const uint32_t *occ, int lds_elems, int max_len, double sign,
-                      int rows, int64_t ws_stride, hipStream_t st)
+                      const void *tw, const uint32_t *occ, int lds_elems, int max_len, double sign, int rows,
+                      int64_t ws_stride, hipStream_t st)
 {
     if (tiles <= 0) return hipSuccess;
     if (rows < 1 || rows > kRowBatch) return hipErrorInvalidValue;
     // dynamic LDS: the lines of one workgroup, then the twiddle table of the longest line
     size_t lds = static_cast<size_t>(lds_elems + max_len) * sizeof(cplx<T>);
-    const T *pc = static_cast<const T *>(precor);
     const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(rows));
     // workgroup size from the longest line of the batch (lines up to kFftSmallLen: 256 threads)
-    if (fft_threads(max_len) == kFftThreadsSmall)
-        hipLaunchKernelGGL((k_fft_pass<T, kFftThreadsSmall>), grid, dim3(kFftThreadsSmall), lds, st, pairs, prefix,
-                           npairs, pass, static_cast<cplx<T> *>(ws), static_cast<const cplx<T> *>(tw), pc, occ,
-                           lds_elems, T(sign), ws_stride);
-    else
-        hipLaunchKernelGGL((k_fft_pass<T, kFftThreads>), grid, dim3(kFftThreads), lds, st, pairs, prefix, npairs, pass,
-                           static_cast<cplx<T> *>(ws), static_cast<const cplx<T> *>(tw), pc, occ, lds_elems, T(sign),
-                           ws_stride);
-    return hipGetLastError();
+    const int threads = fft_threads(max_len);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, pairs, prefix, npairs, pass, static_cast<cplx<T> *>(ws),
+                           static_cast<const cplx<T> *>(tw), occ, lds_elems, T(sign), ws_stride);
+        return hipGetLastError();
+    };
+    return threads == kFftThreadsSmall ? go(k_fft_pass<T, kFftThreadsSmall>) : go(k_fft_pass<T, kFftThreads>);
+}
+
+template <typename T>
+hipError_t launch_fft_two(const PairDev *pairs, const int64_t *prefix, int npairs, int64_t tiles, int pass, void *ws,
+                          const void *tw, const uint32_t *occ, int lds_elems, int threads, double sign, int rows,
+                          int64_t ws_stride, hipStream_t st)
+{
+    if (tiles <= 0) return hipSuccess;
+    if (rows < 1 || rows > kRowBatch || pass < 0 || pass > 1 || threads < 64 || threads > kFft2Threads)
+        return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(rows));
+    const size_t lds = sizeof(cplx<T>) * static_cast<size_t>(lds_elems);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, pairs, prefix, npairs, static_cast<cplx<T> *>(ws),
+                           static_cast<const cplx<T> *>(tw), occ, ws_stride);
+        return hipGetLastError();
+    };
+    if (pass == 0) return sign < 0.0 ? go(k_fft_two<T, 0, -1>) : go(k_fft_two<T, 0, 1>);
+    return sign < 0.0 ? go(k_fft_two<T, 1, -1>) : go(k_fft_two<T, 1, 1>);
 }
 
 template <typename T>
@@ -1584,13 +1779,19 @@ template hipError_t launch_prephase<double>(const PairDev *, const int64_t *, in
                                             const int32_t *, const void *, int64_t, int, void *, void *, int64_t,
                                             double, int, hipStream_t);
 template hipError_t launch_spread<float>(const PairDev *, const SpreadTile *, int64_t, const int32_t *, const void *,
-                                         const void *, int64_t, int, void *, int64_t, int, double, hipStream_t);
+                                         const void *, int64_t, int, void *, int64_t, const void *, int, double,
+                                         hipStream_t);
 template hipError_t launch_spread<double>(const PairDev *, const SpreadTile *, int64_t, const int32_t *, const void *,
-                                          const void *, int64_t, int, void *, int64_t, int, double, hipStream_t);
+                                         const void *, int64_t, int, void *, int64_t, const void *, int, double,
+                                         hipStream_t);
 template hipError_t launch_fft<float>(const PairDev *, const int64_t *, int, int64_t, int, void *, const void *,
-                                      const void *, const uint32_t *, int, int, double, int, int64_t, hipStream_t);
+                                      const uint32_t *, int, int, double, int, int64_t, hipStream_t);
 template hipError_t launch_fft<double>(const PairDev *, const int64_t *, int, int64_t, int, void *, const void *,
-                                       const void *, const uint32_t *, int, int, double, int, int64_t, hipStream_t);
+                                      const uint32_t *, int, int, double, int, int64_t, hipStream_t);
+template hipError_t launch_fft_two<float>(const PairDev *, const int64_t *, int, int64_t, int, void *, const void *,
+                                          const uint32_t *, int, int, double, int, int64_t, hipStream_t);
+template hipError_t launch_fft_two<double>(const PairDev *, const int64_t *, int, int64_t, int, void *, const void *,
+                                          const uint32_t *, int, int, double, int, int64_t, hipStream_t);
 template hipError_t launch_transpose<float>(const PairDev *, const int64_t *, int, int64_t, void *, int, int64_t,
                                             hipStream_t);
 template hipError_t launch_transpose<double>(const PairDev *, const int64_t *, int, int64_t, void *, int, int64_t,

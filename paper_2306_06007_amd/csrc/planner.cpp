@@ -159,6 +159,24 @@ int factor_radices(int32_t n, uint8_t *radix)
     return ns;
 }
 
+// Factors A >= B of an n-point two-factor FFT from the kernel's list, the most
+// equal ones (least registers and threads per line); false if there are none.
+bool factor_two(int32_t n, int dtype, uint8_t f[2])
+{
+    static const int sizes[] = {4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32, 36, 40};
+    for (int a : sizes) {
+        if (a > fft2_max_factor(dtype)) break;
+        if (n % a != 0 || n / a > a) continue;
+        for (int b : sizes)
+            if (a * b == n) {
+                f[0] = static_cast<uint8_t>(a);
+                f[1] = static_cast<uint8_t>(b);
+                return true;
+            }
+    }
+    return false;
+}
+
 // n-point Gauss-Legendre rule on [-1, 1] (Newton iteration on the Legendre
 // three-term recurrence).
 void gauss_legendre(int n, std::vector<double> *x, std::vector<double> *w)
@@ -451,7 +469,8 @@ struct PairGeom {
     int32_t n1[3], n2[3], wstart[3], wcount[3];
     double kscale[3], tscale[3];
     int64_t g1, bx, cy, dz, bufA, bufB;   // bufA, bufB exclude grid 1 (its own region)
-    bool fits;
+    bool fits, two;
+    uint8_t f[2][2];                      // two: factors of the x and y lengths
 };
 
 // Grid sizes of one sub-problem: source half-widths X, effective target
@@ -486,8 +505,9 @@ PairGeom pair_geometry(const double X[3], const double S[3], const Params &p)
     g.bx = wx * n1y * n1z;
     g.cy = wx * wy * n1z;
     g.dz = wx * wy * wz;
-    g.bufA = std::max(g.bx, g.dz);
-    g.bufB = std::max(g.bx, g.cy);
+    g.two = g.n1[0] <= kFft2MaxX && factor_two(g.n2[0], p.dtype, g.f[0]) && factor_two(g.n2[1], p.dtype, g.f[1]);
+    g.bufA = std::max(g.two ? kFft2Block * fft2_blocks(wx) * n1y * n1z : g.bx, g.dz);
+    g.bufB = std::max(g.two ? 0 : g.bx, g.cy);
     // the kernels index inside one grid region with 32-bit arithmetic
     if (g.g1 > kMaxRegionElems || g.bufA > kMaxRegionElems || g.bufB > kMaxRegionElems) g.fits = false;
     return g;
@@ -724,12 +744,14 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
         b.pair0 = static_cast<int64_t>(dp->pairs.size());
         int64_t sumG = 0, sumA = 0, sumB = 0, npts = 0;
         size_t k1 = k;
+        b.two = nufft[k].g.two;   // the x and y passes of a batch are all in two factors or all general
         std::vector<uint8_t> tgt_seen;          // deterministic plans: target chunks of this batch
         if (p.deterministic()) tgt_seen.assign(static_cast<size_t>(tgt.nc), 0);
         while (k1 < nufft.size()) {
             const int64_t gg = nufft[k1].g.g1, a = nufft[k1].g.bufA, bb = nufft[k1].g.bufB;
             const int64_t np = src.off[nufft[k1].i + 1] - src.off[nufft[k1].i];
             if (k1 > k && (sumG + sumA + sumB + gg + a + bb > cap || npts + np > kMaxBatchPts)) break;
+            if (nufft[k1].g.two != b.two) break;
             if (p.deterministic()) {
                 if (tgt_seen[nufft[k1].j]) break;
                 tgt_seen[nufft[k1].j] = 1;
@@ -772,6 +794,16 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
                 pd.wcount[d] = g.wcount[d];
                 pd.nrad[d] = factor_radices(g.n2[d], pd.radix[d]);
                 pd.lines_per_tile[d] = fft_lines(g.n2[d]);
+                int32_t table = g.n2[d];      // key of the twiddle table: the length, or minus it in two factors
+                if (b.two && d < 2) {
+                    const int fa = g.f[d][0], fb = g.f[d][1];
+                    pd.two[d][0] = g.f[d][0];
+                    pd.two[d][1] = g.f[d][1];
+                    const int lines2 = fft2_lines(fa, fb, p.dtype);
+                    b.two_threads[d] = std::max(b.two_threads[d], (lines2 * fa + 63) / 64 * 64);
+                    b.two_lds[d] = std::max(b.two_lds[d], lines2 * fft2_line(fa, fb));
+                    table = -table;
+                }
                 auto key = std::make_pair(g.n1[d], g.n2[d]);
                 auto it = precor_map->find(key);
                 if (it == precor_map->end()) {
@@ -781,7 +813,8 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
                     it = precor_map->emplace(key, off).first;
                 }
                 pd.precor[d] = it->second;
-                if (tw_map->find(g.n2[d]) == tw_map->end()) tw_map->emplace(g.n2[d], 0);
+                if (tw_map->find(table) == tw_map->end()) tw_map->emplace(table, 0);
+                pd.tw[d] = table;             // (the offset, once the tables are laid out)
             }
             pd.bufG = offG;
             pd.bufA = offA;
@@ -798,18 +831,18 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
             offA += g.bufA;
             offB += g.bufB;
             int64_t lines[3] = {static_cast<int64_t>(g.n1[2]) * g.n1[1],
-                                static_cast<int64_t>(g.n1[2]) * g.wcount[0],
+                                static_cast<int64_t>(g.n1[2]) * (b.two ? kFft2Block * fft2_blocks(g.wcount[0]) : g.wcount[0]),
                                 static_cast<int64_t>(g.wcount[0]) * g.wcount[1]};
             const int64_t ntt = static_cast<int64_t>(g.n1[2]) * ((g.n1[1] + kTransposeTile - 1) / kTransposeTile) *
                                 ((g.wcount[0] + kTransposeTile - 1) / kTransposeTile);
             b.ttiles += ntt;
             dp->pre_ttiles.push_back(dp->pre_ttiles.back() + ntt);
             for (int q = 0; q < 3; ++q) {
-                int64_t L = pd.lines_per_tile[q];
+                const int64_t L = b.two && q < 2 ? fft2_lines(pd.two[q][0], pd.two[q][1], p.dtype) : pd.lines_per_tile[q];
                 int64_t tiles = (lines[q] + L - 1) / L;
                 b.tiles[q] += tiles;
                 dp->pre_tiles[q].push_back(dp->pre_tiles[q].back() + tiles);
-                b.lds_elems[q] = std::max<int32_t>(b.lds_elems[q], fft_lds_elems(static_cast<int>(L), g.n2[q]));
+                b.lds_elems[q] = std::max<int32_t>(b.lds_elems[q], fft_lds_elems(pd.lines_per_tile[q], g.n2[q]));
                 b.max_pass_len[q] = std::max(b.max_pass_len[q], g.n2[q]);
             }
             b.pts += pd.src_cnt;
@@ -828,7 +861,7 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
             dp->alg_bytes[HVOX_K_SPREAD] += pd.src_cnt * (16.0 + delta) +
                                             delta * std::min(static_cast<double>(g.g1), pd.src_cnt * w3);
             dp->alg_bytes[HVOX_K_FFT_X] += delta * (static_cast<double>(g.g1) + g.bx);
-            dp->alg_bytes[HVOX_K_TRANSPOSE] += delta * 2.0 * static_cast<double>(g.bx);
+            if (!b.two) dp->alg_bytes[HVOX_K_TRANSPOSE] += delta * 2.0 * static_cast<double>(g.bx);
             dp->alg_bytes[HVOX_K_FFT_Y] += delta * (static_cast<double>(g.bx) + g.cy);
             dp->alg_bytes[HVOX_K_FFT_Z] += delta * (static_cast<double>(g.cy) + g.dz);
             // interpolation: a target's coordinates (16 bytes) and result, and every grid cell
@@ -1061,17 +1094,22 @@ int make_host_plan(const double *uvw, int64_t n_vis, const double *xyz, int64_t 
 
     hp->tw_len.clear();
     hp->tw_off.clear();
+    hp->tw_rows.clear();
     int64_t toff = 0;
     for (auto &kv : tw_map) {
-        hp->tw_len.push_back(kv.first);
+        const int32_t n = std::abs(kv.first);
+        uint8_t f[2] = {0, 0};
+        if (kv.first < 0) factor_two(n, p.dtype, f);
+        hp->tw_len.push_back(n);
         hp->tw_off.push_back(toff);
+        hp->tw_rows.push_back(f[0]);
         kv.second = toff;
-        toff += kv.first;
+        toff += n;
     }
     hp->tw_total = toff;
     for (DirPlan *dp : {&hp->syn, &hp->ana})
         for (PairDev &pd : dp->pairs)
-            for (int d = 0; d < 3; ++d) pd.tw[d] = tw_map[pd.n2[d]];
+            for (int d = 0; d < 3; ++d) pd.tw[d] = tw_map[static_cast<int32_t>(pd.tw[d])];
 
     // per-chunk target scales h = 1 / (2 sigma S_eff) for the deconvolution
     auto tgt_scales = [&](const ChunkSet &tgt, const double fl[3], std::vector<double> *out) {
