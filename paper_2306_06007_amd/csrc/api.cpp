@@ -18,7 +18,7 @@
 
 namespace hvox {
 
-hipError_t launch_zero(double *p, int64_t n, hipStream_t st);
+hipError_t launch_zero(double *p, int64_t n, void *queue, hipStream_t st);
 hipError_t launch_deconv(const double *xyz, int64_t n, const int32_t *chunk_of, const double *ctr,
                          const double *hscale, const double *zq, const double *aq, int nq, int w, double *out,
                          hipStream_t st);
@@ -108,13 +108,14 @@ struct hvox_plan_s {
     void *stage = nullptr;                              // staged sources of one batch (value and footprint)
     double *acc = nullptr;
     double *slab = nullptr;                             // direct sums stored by layer
+    void *queue = nullptr;                              // next item of the direct sum beside NUFFT work
     hipStream_t last_stream = nullptr;
     // a second stream (default priority) the direct sum runs on while the NUFFT
     // batches run on the caller's stream, forked and joined with two events
     hipStream_t side = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     // workgroups of a direct-sum launch beside NUFFT work (persistent grid; 0: one per item)
-    int64_t direct_grid_cap = 0;
+    int64_t direct_grid_cap = 0, direct_help_cap = 0;
     double plan_seconds = 0.0;
     // timing
     std::vector<hvox::TimedLaunch> pending;
@@ -272,11 +273,6 @@ struct Scratch {
 };
 
 // ---- executor -----------------------------------------------------------------
-// largest estimated direct-sum share of a direction's time at which the overlapped
-// direct sum runs on a capped persistent grid (measured on one MI355X: SKA-like cap,
-// direct share 0.75, 609 ms capped vs 624 ms uncapped; LOFAR-like wide field, share
-// 0.93, 14.39 s capped vs 12.71 s uncapped)
-constexpr double kCappedDirectShare = 0.85;
 template <typename T>
 int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, int32_t ntrans, hipStream_t st,
                   const Scratch &sc, bool may_time, bool allow_real = true)
@@ -314,11 +310,6 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
     const bool overlap = may_time && !(p.flags & HVOX_TIMING) && !det && pl->side && !dp.batches.empty() &&
                          !dp.direct.empty();
     hipStream_t dst = overlap ? pl->side : st;
-    // beside a sizeable NUFFT share the direct sum takes a persistent grid capped per
-    // CU, leaving room for the NUFFT kernels; when it is nearly the whole estimated
-    // time (wide fields) it takes one workgroup per item, every CU full of its waves
-    const double direct_share = dp.est_seconds > 0.0 ? dp.est_direct_seconds / dp.est_seconds : 1.0;
-    const int64_t direct_cap = direct_share <= kCappedDirectShare ? pl->direct_grid_cap : 0;
     // rows in groups of up to kRowBatch: the NUFFT sub-problems run in passes of
     // up to hp.rows rows into the group's accumulator rows, the direct sum covers
     // all rows of the group in one launch (its phase factors are shared by the rows)
@@ -331,17 +322,17 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
         const int64_t group = det ? std::min(fit, dp.layers) : (fit >= dp.layers ? dp.layers : 0);
         DirectLaunch dl{dd.direct, 0, dp.direct_tile, sxyz, n_src, txyz, n_tgt, sperm,
                         static_cast<const C *>(in) + static_cast<int64_t>(t0) * n_src, sc.acc, nb, iota, kDirectAtomic,
-                        0, 0, hp.wide_phase, real_only, 0, pl->cis_tab};
+                        0, 0, hp.wide_phase, real_only, 0, pl->cis_tab, pl->queue};
         // stored sums alone make the result when there is nothing else to add: no accumulator
         bool fresh = group > 0 && dp.batches.empty();
         if (!fresh)
-            HVOX_TRY(timed(pl, may_time, HVOX_K_ZERO, st, [&] { return launch_zero(sc.acc, 2 * n_tgt * nb, st); }));
+            HVOX_TRY(timed(pl, may_time, HVOX_K_ZERO, st, [&] { return launch_zero(sc.acc, 2 * n_tgt * nb, pl->queue, st); }));
         if (overlap) {
             // fork: the direct sum starts once the accumulator is clear
             HVOX_TRY(hipEventRecord(pl->fork_ev, st));
             HVOX_TRY(hipStreamWaitEvent(pl->side, pl->fork_ev, 0));
             dl.nitems = static_cast<int64_t>(dp.direct.size());
-            dl.grid_cap = direct_cap;
+            dl.grid_cap = pl->direct_grid_cap;
             HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, dst, [&] { return launch_direct<T>(dl, dst); }));
             HVOX_TRY(hipEventRecord(pl->join_ev, pl->side));
         }
@@ -399,6 +390,11 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
         int layer0 = 0;
         const int64_t nl = static_cast<int64_t>(dp.direct_layer_off.size()) - 1;
         if (overlap) {
+            // the NUFFT batches are done: a second grid on this stream draws from the same queue
+            if (dl.grid_cap > 0) {
+                dl.grid_cap = pl->direct_help_cap;
+                HVOX_TRY(timed(pl, may_time, HVOX_K_DIRECT, st, [&] { return launch_direct<T>(dl, st); }));
+            }
             HVOX_TRY(hipStreamWaitEvent(st, pl->join_ev, 0));   // join before the finalize
         } else if (group > 0) {
             dl.store = kDirectSlab;
@@ -811,6 +807,7 @@ int build_device(hvox_plan_s *pl, hipStream_t st, std::string *err)
     pl->acc = static_cast<double *>(tmp);
     chk(dev_alloc(pl, 16 * static_cast<size_t>(hp.slab_elems), &tmp, true, st), "direct-sum slabs");
     pl->slab = static_cast<double *>(tmp);
+    chk(dev_alloc(pl, 256, &pl->queue, true, st), "direct-sum queue");
     chk(dev_alloc(pl, delta * static_cast<size_t>(hp.ws_elems), &pl->ws, false, st), "workspace");
     int64_t rec_b, val_b;
     stage_layout(hp, &rec_b, &val_b);
@@ -826,6 +823,7 @@ int build_device(hvox_plan_s *pl, hipStream_t st, std::string *err)
         int per_cu = kDirectWgPerCu;
         if (const char *v = std::getenv("HVOX_DIRECT_WG_PER_CU")) per_cu = std::atoi(v);
         pl->direct_grid_cap = per_cu > 0 ? static_cast<int64_t>(per_cu) * ncu : 0;
+        pl->direct_help_cap = static_cast<int64_t>(kDirectHelpPerCu) * ncu;
     }
     chk(hipStreamCreateWithFlags(&pl->side, hipStreamNonBlocking), "direct-sum stream");
     chk(hipEventCreateWithFlags(&pl->fork_ev, hipEventDisableTiming), "fork event");
@@ -1106,6 +1104,7 @@ int hvox_plan_upload(hvox_plan_t plan, void *stream)
         plan->vis_perm = plan->sky_perm = nullptr;
         plan->precor = plan->tw = plan->ws = plan->stage = plan->cis_tab = nullptr;
         plan->acc = plan->slab = nullptr;
+        plan->queue = nullptr;
         plan->syn = DevDir{};
         plan->ana = DevDir{};
         return fail(rc, err);

@@ -70,7 +70,12 @@ constexpr int kDirectNarrowSeg = 128;
 // per data row): whole directions without NUFFT sub-problems, groups of layers in
 // deterministic plans
 constexpr int64_t kSlabElems = int64_t(1) << 20, kSlabElemsDet = int64_t(1) << 22;
-constexpr int kDirectWgPerCu = 8;    // direct-sum workgroups per CU while NUFFT work runs beside it
+// Direct-sum workgroups per CU while NUFFT work runs beside it: a persistent grid fed from a
+// queue, which leaves the two-factor FFT passes the registers they need.  Swept (1 / 2 / 3 / 4 /
+// one workgroup per item, ms): 995,000 x 1M points, float32, synthesis 198 / 184 / 200 / 210 / 211,
+// analysis 232 / 221 / 227 / 233 / 234; 3 km dense mesh 9.1 / 8.7 / 8.8 / 9.0 / 9.0.
+constexpr int kDirectWgPerCu = 2;
+constexpr int kDirectHelpPerCu = 4;  // and those that join them once the NUFFT work is done
 // float32 direct sum: phases of at most this many turns take their fraction from the
 // low word of a float64 sum (kernels.hip, kPhaseMagic); larger ones through a float64 fraction
 constexpr double kMaxMagicTurns = 262144.0;
@@ -193,8 +198,9 @@ struct DirectLaunch {
     int store;                   // DirectStore
     int layer0, layers;          // kDirectSlab: first layer of the launch, layers of a row's slabs
     int wide_phase, real_out;
-    int64_t grid_cap;            // > 0: persistent grid of at most this many workgroups
+    int64_t grid_cap;            // > 0: persistent grid of at most this many workgroups, fed from the queue
     const void *ctab;            // float64 plans: the phase table
+    void *queue;                 // next item of a persistent grid (64 bits, zero before the launch)
 };
 
 // ---- host-side plan pieces -------------------------------------------------

@@ -98,9 +98,11 @@ static_assert(int64_t(kFftMaxLen / kTileX) * (kFftMaxLen / kTileY) * (kFftMaxLen
 // ---------------------------------------------------------------------------
 // accumulator clear
 // ---------------------------------------------------------------------------
-__global__ void k_zero(double *__restrict__ p, int64_t n)
+// (and of the direct sum's item queue, if given)
+__global__ void k_zero(double *__restrict__ p, int64_t n, unsigned long long *__restrict__ queue)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (queue && i == 0) *queue = 0;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (; i < n; i += stride) p[i] = 0.0;
 }
@@ -759,7 +761,7 @@ template <int MAX, typename F> __device__ __forceinline__ void fft2_switch(int r
 {
 #define HVOX_CASE(R) case R: if constexpr (R <= MAX) f(std::integral_constant<int, R>{}); break;
     switch (r) {
-        HVOX_CASE(4) HVOX_CASE(5) HVOX_CASE(6) HVOX_CASE(8) HVOX_CASE(9) HVOX_CASE(10) HVOX_CASE(12) HVOX_CASE(15)
+        HVOX_CASE(3) HVOX_CASE(4) HVOX_CASE(5) HVOX_CASE(6) HVOX_CASE(8) HVOX_CASE(9) HVOX_CASE(10) HVOX_CASE(12) HVOX_CASE(15)
         HVOX_CASE(16) HVOX_CASE(18) HVOX_CASE(20) HVOX_CASE(24) HVOX_CASE(25) HVOX_CASE(27) HVOX_CASE(30)
         HVOX_CASE(32) HVOX_CASE(36) HVOX_CASE(40)
     default: break;
@@ -780,6 +782,9 @@ __global__ __launch_bounds__(kFft2Threads, sizeof(T) == 8 ? 2 : 3) void k_fft_tw
     const cplx<T> *__restrict__ twtab, const uint32_t *__restrict__ occ, int64_t ws_stride)
 {
     static_assert(kTileX == 32 && kFft2MaxX <= 32 * kTileX, "a line's tiles fit a word");
+    // over the direct sum's wavefronts, which never wait for memory (3 km dense mesh, automatic
+    // choice: 8.7 -> 8.2 ms; the other NUFFT kernels gain nothing from it beside a long direct sum)
+    __builtin_amdgcn_s_setprio(2);
     constexpr T s = T(SIGN);   // (a constant: the quarter turns of the DFTs cost nothing)
     constexpr int kType = sizeof(T) == 8 ? HVOX_F64 : HVOX_F32, kMax = fft2_max_factor(kType), kC = kFft2Block;
     constexpr uint32_t kB = sizeof(cplx<T>);
@@ -1413,11 +1418,12 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
     }
 }
 
-// One workgroup per work item, or (persistent launches, grid smaller than
-// the item count) each workgroup loops over items blockIdx.x, + gridDim.x,
-// ...: a capped grid leaves room on every CU for the kernels of the NUFFT
-// sub-problems running beside the direct sum on another stream.  Items stay
-// source-segment-major across consecutive workgroups either way.
+// One workgroup per work item, or (persistent launches) workgroups that take
+// items from a queue until it is empty: a capped grid leaves room on every CU
+// for the kernels of the NUFFT sub-problems running beside the direct sum on
+// another stream, and workgroups of CUs that those kernels slow down take fewer items (a
+// fixed share per workgroup cost 5% with 8 workgroups per CU and 9% with 5, even with the GPU
+// to itself).  Items stay source-segment-major across consecutive workgroups either way.
 template <typename T, int NT, int TILE, bool WIDE>
 __global__ __launch_bounds__(kDirectThreads) void k_direct(const DirectItem *__restrict__ items, int64_t nitems,
                                                            const double *__restrict__ sxyz, int64_t nsrc,
@@ -1426,7 +1432,8 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct(const DirectItem *__r
                                                            const cplx<T> *__restrict__ in, int64_t in_stride,
                                                            double *__restrict__ acc, int64_t acc_stride, double iota,
                                                            int store, int layer0, int layers, int real_out,
-                                                           const double2 *__restrict__ ctab)
+                                                           const double2 *__restrict__ ctab,
+                                                           unsigned long long *__restrict__ queue)
 {
     static_assert(kDirectSrcTile == kDirectThreads && kDirectTile == 2 * kDirectThreads, "direct tiling");
     static_assert(kDirectSrcTile % 4 == 0, "the staged tile is walked in fours");
@@ -1437,9 +1444,23 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct(const DirectItem *__r
         for (int i = threadIdx.x; i < kCisTab; i += kDirectThreads) ltab[i] = ctab[i];
         // the first item's staging barrier orders these writes before any read
     }
-    for (int64_t w = blockIdx.x; w < nitems; w += gridDim.x)   // (staging starts with a barrier)
+    auto item = [&](int64_t w) {   // (starts with a barrier)
         direct_item<T, NT, TILE, WIDE>(items[w], sxyz, nsrc, txyz, ntgt, perm, in, in_stride, acc, acc_stride, iota,
                                        store, layer0, layers, real_out, lxyz, lc, ltab);
+    };
+    if (!queue) {
+        if (blockIdx.x < nitems) item(blockIdx.x);
+        return;
+    }
+    __shared__ int64_t next;
+    for (;;) {
+        if (threadIdx.x == 0) next = static_cast<int64_t>(atomicAdd(queue, 1ull));
+        __syncthreads();
+        const int64_t w = next;
+        if (w >= nitems) return;   // every workgroup draws past the last item once
+        item(w);
+        __syncthreads();           // `next` is read, the staged sources are free
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1543,10 +1564,11 @@ static inline unsigned blocks_for(int64_t n, int per, int64_t cap)
     return static_cast<unsigned>(b);
 }
 
-hipError_t launch_zero(double *p, int64_t n, hipStream_t st)
+hipError_t launch_zero(double *p, int64_t n, void *queue, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero, dim3(blocks_for(n, 256 * 8, 65536)), dim3(256), 0, st, p, n);
+    hipLaunchKernelGGL(k_zero, dim3(blocks_for(n, 256 * 8, 65536)), dim3(256), 0, st, p, n,
+                       static_cast<unsigned long long *>(queue));
     return hipGetLastError();
 }
 
@@ -1705,10 +1727,12 @@ static hipError_t direct_grid(const DirectLaunch &d, hipStream_t st)
         hipLaunchKernelGGL((k_direct<T, NT, TILE, WIDE>), dim3(static_cast<unsigned>(grid)), dim3(kDirectThreads), 0, st,
                            items, n, d.sxyz, d.nsrc, d.txyz, d.ntgt, d.perm, static_cast<const cplx<T> *>(d.in), d.nsrc,
                            d.acc, 2 * d.ntgt, d.iota, d.store, d.layer0, d.layers, d.real_out,
-                           static_cast<const double2 *>(d.ctab));
+                           static_cast<const double2 *>(d.ctab),
+                           static_cast<unsigned long long *>(d.grid_cap > 0 ? d.queue : nullptr));
         return hipGetLastError();
     };
-    // persistent: at most grid_cap workgroups looping over the items
+    // persistent: at most grid_cap workgroups taking items from the queue
+    if (d.grid_cap > 0 && d.queue == nullptr) return hipErrorInvalidValue;
     if (d.grid_cap > 0)
         return go(d.items, d.nitems, std::min<int64_t>(std::min<int64_t>(d.grid_cap, d.nitems), kMaxLaunchBlocks));
     // one workgroup per item, in launches of at most kMaxLaunchBlocks workgroups

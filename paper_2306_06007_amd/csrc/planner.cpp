@@ -163,7 +163,7 @@ int factor_radices(int32_t n, uint8_t *radix)
 // equal ones (least registers and threads per line); false if there are none.
 bool factor_two(int32_t n, int dtype, uint8_t f[2])
 {
-    static const int sizes[] = {4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32, 36, 40};
+    static const int sizes[] = {3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32, 36, 40};
     for (int a : sizes) {
         if (a > fft2_max_factor(dtype)) break;
         if (n % a != 0 || n / a > a) continue;
@@ -719,10 +719,15 @@ void plan_direction(const HostPlan &hp, const DirInputs &in, DirPlan *dp,
     // Deterministic plans: sub-problems source-chunk-major, and a batch never holds two
     // sub-problems of one target chunk, so the interpolation of a batch adds into every
     // target at most once (plain read-modify-write, no atomics) and the batches add in order.
+    // The sub-problems whose x and y passes run in two factors come first: a batch holds only
+    // one kind.
     if (p.deterministic())
         std::stable_sort(nufft.begin(), nufft.end(), [](const Cand &a, const Cand &b) {
+            if (a.g.two != b.g.two) return a.g.two;
             return a.i != b.i ? a.i < b.i : a.j < b.j;
         });
+    else
+        std::stable_partition(nufft.begin(), nufft.end(), [](const Cand &c) { return c.g.two; });
     // group NUFFT sub-problems into batches sharing the workspace
     dp->pairs.clear();
     dp->batches.clear();
@@ -896,7 +901,7 @@ int64_t device_bytes_bound(const HostPlan &hp)
     const int64_t staged = p.dtype == HVOX_F64 ? sizeof(StagedSrc<double>) : sizeof(StagedSrc<float>);
     int64_t b = 24 * (nv + np) + 4 * (nv + np) + 8 * (nv + np) + 4 * (nv + np);   // coords, perms, deconv, chunk ids
     b += 16 * static_cast<int64_t>(kRowBatch) * std::max(nv, np);                // accumulator
-    b += 16 * hp.slab_elems;                                                     // direct sums stored per layer
+    b += 16 * hp.slab_elems + 256;                                               // direct sums stored per layer, queue
     b += prec * static_cast<int64_t>(hp.precor_nu.size()) + delta * hp.tw_total;
     if (p.dtype == HVOX_F64) b += 16 * kCisTab;                                 // direct-sum phase table
     const int nq = 2 * std::max(p.w, p.w2) + 60;
