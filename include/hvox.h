@@ -231,6 +231,10 @@ int hvox_synthesis(hvox_plan_t plan, const void *sky, void *vis, int32_t ntrans,
  * With HVOX_REAL_SKY the imaginary part of sky is set to 0. */
 int hvox_analysis(hvox_plan_t plan, const void *vis, void *sky, int32_t ntrans, void *stream);
 
+/* hvox_analysis as on a HVOX_REAL_SKY plan, whatever the plan's flags: the
+ * imaginary part of sky is set to 0 (the gradient with respect to a real sky). */
+int hvox_analysis_real(hvox_plan_t plan, const void *vis, void *sky, int32_t ntrans, void *stream);
+
 /* For callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.
  * Runs synthesis (direction 0, as hvox_synthesis) or analysis (direction 1,

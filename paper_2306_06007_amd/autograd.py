@@ -21,10 +21,10 @@ class HvoxSynthesis(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g):
-        gx = ctx.plan.analysis(g.contiguous())
-        if ctx.real_input:
-            gx = gx.real.to(ctx.in_dtype)
-        return gx, None
+        if ctx.real_input:   # only the real part of A^H g is wanted
+            gx = getattr(ctx.plan, "_analysis_real", ctx.plan.analysis)(g.contiguous())
+            return gx.real.to(ctx.in_dtype), None
+        return ctx.plan.analysis(g.contiguous()), None
 
 
 class HvoxAnalysis(torch.autograd.Function):

@@ -275,7 +275,7 @@ struct Scratch {
 // ---- executor -----------------------------------------------------------------
 template <typename T>
 int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, int32_t ntrans, hipStream_t st,
-                  const Scratch &sc, bool may_time, bool allow_real = true)
+                  const Scratch &sc, bool may_time, bool allow_real = true, bool want_real = false)
 {
     const HostPlan &hp = pl->hp;
     const Params &p = hp.prm;
@@ -290,7 +290,7 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
     const int32_t *sperm = pre ? nullptr : (synthesis ? pl->sky_perm : pl->vis_perm);
     const int32_t *tperm = pre ? nullptr : (synthesis ? pl->vis_perm : pl->sky_perm);
     const double iota = synthesis ? -1.0 : 1.0;
-    const int real_only = (allow_real && !synthesis && (p.flags & HVOX_REAL_SKY)) ? 1 : 0;
+    const int real_only = (allow_real && !synthesis && (want_real || (p.flags & HVOX_REAL_SKY))) ? 1 : 0;
     const int det = p.deterministic() ? 1 : 0;
     using C = typename std::conditional<sizeof(T) == 4, float2, double2>::type;
     hipError_t e = hipSuccess;
@@ -446,7 +446,8 @@ Scratch plan_scratch(const hvox_plan_s *pl)
     return Scratch{pl->ws, pl->stage, pl->acc, xval, pl->slab};
 }
 
-int transform(hvox_plan_s *pl, bool synthesis, const void *in, void *out, int32_t ntrans, void *stream)
+int transform(hvox_plan_s *pl, bool synthesis, const void *in, void *out, int32_t ntrans, void *stream,
+              bool want_real = false)
 {
     if (!pl) return fail(HVOX_ERR_STATE, "NULL plan");
     if (pl->host_only) return fail(HVOX_ERR_STATE, "host-only plan cannot run transforms (hvox_plan_upload first)");
@@ -459,8 +460,9 @@ int transform(hvox_plan_s *pl, bool synthesis, const void *in, void *out, int32_
     if (cur != pl->device) return fail(HVOX_ERR_STATE, "the plan's device is not the current device");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Scratch sc = plan_scratch(pl);
-    if (pl->hp.prm.dtype == HVOX_F64) return run_direction<double>(pl, synthesis, in, out, ntrans, st, sc, true);
-    return run_direction<float>(pl, synthesis, in, out, ntrans, st, sc, true);
+    if (pl->hp.prm.dtype == HVOX_F64)
+        return run_direction<double>(pl, synthesis, in, out, ntrans, st, sc, true, true, want_real);
+    return run_direction<float>(pl, synthesis, in, out, ntrans, st, sc, true, true, want_real);
 }
 
 // Direction-dependent gains A_k(r_n) = sum_t a[t][k] b[t][n]: per data row, the
@@ -1076,6 +1078,15 @@ int hvox_analysis(hvox_plan_t plan, const void *vis, void *sky, int32_t ntrans, 
         return transform(plan, false, vis, sky, ntrans, stream);
     } catch (...) {
         return fail(HVOX_ERR_HIP, "unexpected failure in hvox_analysis");
+    }
+}
+
+int hvox_analysis_real(hvox_plan_t plan, const void *vis, void *sky, int32_t ntrans, void *stream)
+{
+    try {
+        return transform(plan, false, vis, sky, ntrans, stream, true);
+    } catch (...) {
+        return fail(HVOX_ERR_HIP, "unexpected failure in hvox_analysis_real");
     }
 }
 

@@ -85,7 +85,7 @@ class HvoxStats(ctypes.Structure):
 
 
 EXPORTS = ("hvox_plan", "hvox_plan_upload", "hvox_synthesis", "hvox_transform_noalloc", "hvox_synthesis_dde",
-           "hvox_analysis_dde", "hvox_analysis", "hvox_free", "hvox_plan_info",
+           "hvox_analysis_dde", "hvox_analysis", "hvox_analysis_real", "hvox_free", "hvox_plan_info",
            "hvox_plan_permutation", "hvox_plan_chunks", "hvox_stats", "hvox_stats_reset", "hvox_set_timing",
            "hvox_kernel_params", "hvox_alg1", "hvox_partition", "hvox_error_string",
            "hvox_last_error", "hvox_version")
@@ -108,7 +108,7 @@ def load_library():
     lib.hvox_plan.restype = ctypes.c_int
     lib.hvox_plan.argtypes = [dp, ctypes.c_int64, dp, ctypes.c_int64, ctypes.c_double, ctypes.c_int32,
                               ctypes.POINTER(HvoxOpts), vp, ctypes.POINTER(vp)]
-    for name in ("hvox_synthesis", "hvox_analysis"):
+    for name in ("hvox_synthesis", "hvox_analysis", "hvox_analysis_real"):
         f = getattr(lib, name)
         f.restype = ctypes.c_int
         f.argtypes = [vp, vp, vp, ctypes.c_int32, vp]
@@ -385,6 +385,10 @@ class Plan:
     def analysis(self, vis, out=None, stream=None):
         """I[t, n] = sum_k vis[t, k] exp(+2 pi i <p_k, r_n>)."""
         return self._transform(self._lib.hvox_analysis, vis, self.n_vis, self.n_pix, "vis", out, stream)
+
+    def _analysis_real(self, vis):
+        """analysis with the imaginary part left out (set to 0): the direct sum then skips half its multiply-adds."""
+        return self._transform(self._lib.hvox_analysis_real, vis, self.n_vis, self.n_pix, "vis", None, None)
 
     def upload(self, stream=None):
         """Create the device part of a host-only plan (hvox_plan_upload)."""

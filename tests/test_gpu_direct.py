@@ -88,3 +88,15 @@ def test_non_finite_imaginary_part(value):
     with hv.Plan(uvw, xyz, 0.0, "f32") as p:
         V = p.synthesis(torch.as_tensor(sky).to("cuda", torch.complex64)).cpu().numpy()
     assert not np.isfinite(V.view(np.float32)).reshape(-1, 2).all(axis=1).any()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_real_part_of_analysis(dtype):
+    """The gradient's adjoint of a plan without the real-sky flag: the real part of analysis, imaginary part 0."""
+    cd = torch.complex64 if dtype == "f32" else torch.complex128
+    uvw, xyz, turns, rng = _case(601, 515, 1.0)
+    vis = W.complex_normal(2, 601, rng).astype(np.complex64 if dtype == "f32" else np.complex128).astype(np.complex128)
+    with hv.Plan(uvw, xyz, 0.0, dtype) as p:
+        sky = p._analysis_real(torch.as_tensor(vis).to("cuda", cd)).cpu().numpy()
+    assert (sky.imag == 0).all()
+    assert (np.abs(sky.real - oracle.analysis(uvw, xyz, vis).real) <= _bound(dtype, turns, vis)).all()
