@@ -171,21 +171,24 @@ def roofline_entry(st, dtype, name=None, rows=1, mode="auto"):
 ALG_OPS_PER_TERM = 30.0
 # VALU instructions issued per (target, source, data row) by the direct
 # kernel's inner loop, counted from its gfx950 assembly (the loop that reads
-# the staged sources from LDS; LDS reads and scalar loop control excluded), by
-# plan precision and rows per launch.  Per iteration of 4 sources x 2 targets:
-# the float64 dot product and reduction to a fraction of a turn (shared by the
-# rows), float32: conversion and hardware sine and cosine (shared), float64:
-# the 1024-entry phase table's index and remainder, the remainder's Taylor
-# sine and cosine and the rotation by the table entry (shared), then one
-# complex multiply-accumulate per row.  Each is one lane-operation per lane.
-VALU_OPS_PER_TERM = {("f32", 1): 89 / 8, ("f32", 2): 121 / 16, ("f32", 3): 153 / 24, ("f32", 4): 185 / 32,
-                     ("f64", 1): 178 / 8, ("f64", 2): 210 / 16, ("f64", 3): 242 / 24, ("f64", 4): 274 / 32}
+# the staged sources from LDS, complex source values, 512-target tiles; LDS
+# reads and scalar loop control excluded), by plan precision and rows per
+# launch.  Per iteration of 4 sources x 2 targets: float32, the float64 dot
+# product that leaves the fraction of a turn in its low word, its extraction and
+# hardware sine and cosine (shared by the rows); float64, the dot product, the
+# 1024-entry phase table's index and remainder, the remainder's Taylor sine and
+# cosine and the rotation by the table entry (shared); then one complex
+# multiply-accumulate per row.  Each is one lane-operation per lane.  Tiles whose
+# source values are all real (a sky of intensities) issue two instructions less
+# per term-row, so such a synthesis can pass the complex loop's bound.
+VALU_OPS_PER_TERM = {("f32", 1): 81 / 8, ("f32", 2): 113 / 16, ("f32", 3): 145 / 24, ("f32", 4): 177 / 32,
+                     ("f64", 1): 170 / 8, ("f64", 2): 202 / 16, ("f64", 3): 234 / 24, ("f64", 4): 266 / 32}
 # Lane-cycles per term-row of the same loops at the per-class issue rates
 # (float32 arithmetic 1/2 cycle, hardware sine / cosine 2, the rest 1): float32
-# 32 / 64 / 96 / 128 float32 + 16 transcendental + 41 other per 8 / 16 / 24 / 32
+# 32 / 64 / 96 / 128 float32 + 16 transcendental + 33 other per 8 / 16 / 24 / 32
 # term-rows; float64 has no float32 or transcendental instructions.
-VALU_CYCLES_PER_TERM = {("f32", 1): 89 / 8, ("f32", 2): 105 / 16, ("f32", 3): 121 / 24, ("f32", 4): 137 / 32,
-                        ("f64", 1): 178 / 8, ("f64", 2): 210 / 16, ("f64", 3): 242 / 24, ("f64", 4): 274 / 32}
+VALU_CYCLES_PER_TERM = {("f32", 1): 81 / 8, ("f32", 2): 97 / 16, ("f32", 3): 113 / 24, ("f32", 4): 129 / 32,
+                        ("f64", 1): 170 / 8, ("f64", 2): 202 / 16, ("f64", 3): 234 / 24, ("f64", 4): 266 / 32}
 
 
 def host_cpu_model() -> str:

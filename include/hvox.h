@@ -70,7 +70,8 @@ typedef enum { HVOX_F32 = 0, HVOX_F64 = 1 } hvox_dtype;
 #define HVOX_DETERMINISTIC   0x10 /* bit-reproducible results: no floating-point atomics.  Spreading tiles
                                      are never split and list their sources in index order, sub-problems
                                      sharing a target chunk never run in the same launch, and direct-sum
-                                     blocks add into the accumulator layer by layer in a fixed order.
+                                     blocks add up layer by layer in a fixed order (a group of layers
+                                     per launch where their partial sums fit the plan's memory).
                                      Slower on crowded grids and on plans with few target chunks. */
 
 typedef struct hvox_plan_s *hvox_plan_t;

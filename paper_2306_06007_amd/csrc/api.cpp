@@ -816,9 +816,10 @@ int build_device(hvox_plan_s *pl, hipStream_t st, std::string *err)
     if (hp.max_pts > 0)
         chk(dev_alloc(pl, static_cast<size_t>(rec_b + val_b), &pl->stage, true, st), "source staging");
     if (rc) return bail(rc);
-    // the direct sum's stream and the fork / join events; its grid is capped at
-    // kDirectWgPerCu workgroups per CU so the NUFFT kernels find room beside it
-    // (HVOX_DIRECT_WG_PER_CU overrides the cap for tuning, 0 = uncapped)
+    // the direct sum's stream and the fork / join events; beside NUFFT work its grid is
+    // kDirectWgPerCu workgroups per CU that take items from a queue, so the NUFFT kernels
+    // find room, joined by kDirectHelpPerCu more once the batches are done
+    // (HVOX_DIRECT_WG_PER_CU overrides the first for tuning, 0 = one workgroup per item)
     {
         int ncu = 0;
         chk(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, pl->device), "CU count");

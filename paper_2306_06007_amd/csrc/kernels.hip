@@ -12,13 +12,17 @@
 //                 the x pass reads the others as zeros;
 //  * grids:       per batch of sub-problems and per data row of a pass one
 //                 workspace copy with three regions:
-//                 G holds every pair's grid 1 as [n1z][n1y][n1x]; the x pass
-//                 writes its kept window line-major to B ([n1z][n1y][wx]), a
-//                 tiled transpose moves it to A ([n1z][wx][n1y]), the y pass
-//                 writes B ([n1z][wx][wy]), and the z pass reads its lines
+//                 G holds every pair's grid 1 as [n1z][n1y][n1x]; where both
+//                 lengths have two factors the x pass writes its kept window to
+//                 A in blocks of four columns ([n1z][wx/4][n1y][4]), which the y
+//                 pass reads; other lengths go line-major to B ([n1z][n1y][wx])
+//                 and through a tiled transpose to A ([n1z][wx][n1y]).  The y
+//                 pass writes B ([n1z][wx][wy]), and the z pass reads its lines
 //                 strided and writes A as [wx][wy][wz] (z fastest), which the
 //                 interpolation reads;
-//  * accumulator: float64 complex per target (chunk order).
+//  * accumulator: float64 complex per target (chunk order); directions without
+//                 NUFFT sub-problems and deterministic plans may keep partial sums
+//                 of the direct sum beside it ([layer][target]), added up in order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -32,9 +32,11 @@ constexpr double kPi = 3.14159265358979323846;
 // below and the spreading / interpolation kernels ~4e11 kernel-cell updates/s
 // in float32 and ~8e11 in float64 (its 14-wide footprints fill more lanes of
 // a wavefront, and float64 FMAs issue at the float32 rate); the direct
-// kernel 3.0e12 (float32) and 1.35e12 (float64) terms/s.  A sweep of the
-// decision threshold on the SKA-like and dense DCOS workloads puts the
-// fastest split at these rates (threshold 1).
+// kernel 3.0e12 (float32) and 1.35e12 (float64) terms/s.  These are not the
+// rates of the kernels run alone (float32 direct sum 3.3e12 to 3.9e12, FFT passes
+// without the transpose): the two share the GPU, and the decision they give was
+// swept again with today's kernels, where threshold 1 is within 1% of the best
+// on the SKA-like and dense DCOS workloads.
 struct Rates {
     double hbm_bytes_per_s;     // effective streaming rate of the grid passes
     double cells_per_s;         // spread/interp kernel-cell updates
@@ -557,9 +559,9 @@ double pair_direct_seconds(int64_t ns, int64_t nt, int dtype)
 
 // Cost of `rows` data rows relative to one: the direct kernel evaluates each
 // phase factor once for up to kRowBatch rows, so every further row of a group
-// adds only its multiply-adds (about 2 of the 11 issue cycles of a float32
-// term and 4 of the 22 of a float64 term, from the direct kernel's inner-loop
-// instruction counts); a NUFFT sub-problem repeats every stage per row.
+// adds only its multiply-adds (2 of the 10 to 11 issue cycles of a float32
+// term and 4 of the 21 to 22 of a float64 term, from the direct kernel's
+// inner-loop instruction counts); a NUFFT sub-problem repeats every stage per row.
 double direct_rows_factor(int rows, int dtype)
 {
     const double extra = dtype == HVOX_F64 ? 4.0 / 22.25 : 2.0 / 11.125;
