@@ -32,11 +32,15 @@ constexpr double kPi = 3.14159265358979323846;
 // below and the spreading / interpolation kernels ~4e11 kernel-cell updates/s
 // in float32 and ~8e11 in float64 (its 14-wide footprints fill more lanes of
 // a wavefront, and float64 FMAs issue at the float32 rate); the direct
-// kernel 3.0e12 (float32) and 1.35e12 (float64) terms/s.  These are not the
-// rates of the kernels run alone (float32 direct sum 3.3e12 to 3.9e12, FFT passes
-// without the transpose): the two share the GPU, and the decision they give was
-// swept again with today's kernels, where threshold 1 is within 1% of the best
-// on the SKA-like and dense DCOS workloads.
+// kernel 3.0e12 (float32) and 1.35e12 (float64) terms/s.  The kernels have
+// become faster than that (float32 direct sum 3.3e12 to 3.9e12, grid passes
+// without the transpose), the grids by more: with the decision threshold at 0.7
+// / 1 / 1.2 / 1.5 / 2 the SKA-like float32 synthesis takes 215 / 188 / 181 / 178 /
+// 195 ms, its analysis 253 / 221 / 212 / 210 / 215 ms, the 3 km dense mesh 8.5 / 8.5 /
+// 8.6 / 8.5 / 8.8 ms.  The rates stay: a higher threshold moves terms from the direct
+// sum (errors of 1e-7) to grids (errors of the order of eps), and what a plan
+// delivers should not lose accuracy for those 4 to 6%.  Callers choose
+// direct_threshold themselves where they prefer the time.
 struct Rates {
     double hbm_bytes_per_s;     // effective streaming rate of the grid passes
     double cells_per_s;         // spread/interp kernel-cell updates
