@@ -1012,9 +1012,11 @@ __device__ __forceinline__ void cis_tab(double u, const double2 *tab, double &c,
 }
 
 // exp(2 pi i <a, b>) in float64: the products split exactly into a rounded
-// part, reduced to a fraction of a turn, and its rounding error
+// part, reduced to a fraction of a turn, and its rounding error (no contraction:
+// a fused p - rint(p) would count the error twice)
 __device__ __forceinline__ void cis_dot(const double a[3], const double b[3], double &c, double &s)
 {
+#pragma clang fp contract(off)
     double f = 0.0, e = 0.0;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -1434,12 +1436,15 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
             }
             cis_dot(p0, ref, e0c, e0s);
             cis_dot(p1, ref, e1c, e1s);
+            // (fused by hand: left to the compiler, which product takes the fused form differs
+            // between the instances for one row and for several, and with it a row's last bits)
 #pragma unroll
             for (int r = 0; r < NT; ++r) {
-                a0r[r] += b0r[r] * e0c - b0i[r] * e0s;
-                a0i[r] += b0r[r] * e0s + b0i[r] * e0c;
-                a1r[r] += b1r[r] * e1c - b1i[r] * e1s;
-                a1i[r] += b1r[r] * e1s + b1i[r] * e1c;
+#pragma clang fp contract(off)
+                a0r[r] += fma(b0r[r], e0c, -b0i[r] * e0s);
+                a0i[r] += fma(b0r[r], e0s, b0i[r] * e0c);
+                a1r[r] += fma(b1r[r], e1c, -b1i[r] * e1s);
+                a1i[r] += fma(b1r[r], e1s, b1i[r] * e1c);
             }
         }
     }
