@@ -71,7 +71,9 @@ typedef enum { HVOX_F32 = 0, HVOX_F64 = 1 } hvox_dtype;
                                      are never split and list their sources in index order, sub-problems
                                      sharing a target chunk never run in the same launch, and direct-sum
                                      blocks add up layer by layer in a fixed order (a group of layers
-                                     per launch where their partial sums fit the plan's memory).
+                                     per launch where their partial sums fit the plan's memory); a row's
+                                     bits depend neither on the rows that share its call nor on the entry
+                                     point (hvox_transform_noalloc included).
                                      Slower on crowded grids and on plans with few target chunks. */
 
 typedef struct hvox_plan_s *hvox_plan_t;

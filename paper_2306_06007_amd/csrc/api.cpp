@@ -47,7 +47,7 @@ hipError_t launch_direct(const DirectLaunch &, hipStream_t);
 hipError_t launch_add_layers(double *, int64_t, const double *, int, int, const int32_t *, int, int, hipStream_t);
 template <typename T>
 hipError_t launch_finalize(const double *, int64_t, const int32_t *, void *, int, const double *, int, int,
-                           const int32_t *, int, hipStream_t);
+                           const int32_t *, int, int, hipStream_t);
 template <typename T>
 hipError_t launch_dde_scale(const void *, const void *, void *, int64_t, int, int, hipStream_t);
 template <typename T>
@@ -424,7 +424,7 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
         HVOX_TRY(timed(pl, may_time, HVOX_K_FINAL, st, [&] {
             return launch_finalize<T>(fresh ? nullptr : sc.acc, n_tgt, tperm,
                                       static_cast<C *>(out) + static_cast<int64_t>(t0) * n_tgt, real_only, slab, layer0,
-                                      static_cast<int>(group), dd.tgt_layers, nb, st);
+                                      static_cast<int>(group), dd.tgt_layers, det, nb, st);
         }));
         for (int k = 0; k < HVOX_K_COUNT; ++k) {
             pl->stats.alg_bytes[k] += dp.alg_bytes[k] * nb;

@@ -1570,7 +1570,9 @@ __global__ void k_add_layers(double2 *__restrict__ acc, int64_t n, const double2
 // order (the inverse of the chunk-order gather, Sect. 4 Fig. 5).  The sums are
 // the accumulator (if any) and the last stored layers (if any); G = 1 << lg lanes share
 // a target's layers, each every G-th of them, so that few targets with many
-// layers still fill the GPU.  Grid y: data rows.
+// layers still fill the GPU.  With one lane (deterministic plans) the layers are
+// added one after another, as k_add_layers and in-place items add them: the order
+// does not depend on how many layers a launch stores.  Grid y: data rows.
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ void k_finalize(const double2 *__restrict__ acc, int64_t n, const int32_t *__restrict__ perm,
@@ -1584,6 +1586,7 @@ __global__ void k_finalize(const double2 *__restrict__ acc, int64_t n, const int
     if (slab) {
         slab += (int64_t)blockIdx.y * layers * n + k;
         const int m = min(layers, tgt_layers[k] - layer0);
+#pragma unroll 8
         for (int l = g; l < m; l += 1 << lg) {
             const double2 s = slab[l * n];
             v.x += s.x;
@@ -1862,14 +1865,15 @@ hipError_t launch_add_layers(double *acc, int64_t n, const double *slab, int lay
 
 template <typename T>
 hipError_t launch_finalize(const double *acc, int64_t n, const int32_t *perm, void *out, int real_only,
-                           const double *slab, int layer0, int layers, const int32_t *tgt_layers, int rows,
+                           const double *slab, int layer0, int layers, const int32_t *tgt_layers, int det, int rows,
                            hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
     // lanes per target: up to a wavefront, while the targets alone do not fill the GPU
-    // (2^18 threads) and every lane keeps two layers
+    // (2^18 threads) and every lane keeps two layers; one in deterministic plans, where the layers
+    // of a launch depend on the rows of the call and on its scratch, but the sum's order must not
     int lg = 0;
-    while (slab && lg < 6 && (n << lg) < (int64_t(1) << 18) && (4 << lg) <= layers) ++lg;
+    while (slab && !det && lg < 6 && (n << lg) < (int64_t(1) << 18) && (4 << lg) <= layers) ++lg;
     hipLaunchKernelGGL(k_finalize<T>, dim3(blocks_for(n << lg, 256, INT32_MAX), static_cast<unsigned>(rows)), dim3(256),
                        0, st, reinterpret_cast<const double2 *>(acc), n, perm, static_cast<cplx<T> *>(out), real_only,
                        reinterpret_cast<const double2 *>(slab), layer0, layers, tgt_layers, lg);
@@ -1935,8 +1939,8 @@ template hipError_t launch_dde_combine<float>(const void *, const void *, void *
 template hipError_t launch_dde_combine<double>(const void *, const void *, void *, int64_t, int, int, int,
                                                hipStream_t);
 template hipError_t launch_finalize<float>(const double *, int64_t, const int32_t *, void *, int, const double *, int, int,
-                                             const int32_t *, int, hipStream_t);
+                                             const int32_t *, int, int, hipStream_t);
 template hipError_t launch_finalize<double>(const double *, int64_t, const int32_t *, void *, int, const double *, int, int,
-                                             const int32_t *, int, hipStream_t);
+                                             const int32_t *, int, int, hipStream_t);
 
 }  // namespace hvox
