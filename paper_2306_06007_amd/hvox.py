@@ -7,6 +7,7 @@ library has not been built, importing works but every call raises
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional
@@ -331,6 +332,17 @@ class Plan:
             return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
+    def _on(self, stream):
+        """Context in which the copies that a call makes of its tensors are ordered with its kernels."""
+        if stream is None:
+            return contextlib.nullcontext()
+        torch = _torch()
+        if not hasattr(stream, "cuda_stream"):
+            handle = int(stream)
+            stream = (torch.cuda.ExternalStream(handle, device=self.device) if handle
+                      else torch.cuda.default_stream(self.device))
+        return torch.cuda.stream(stream)
+
     def _check_runnable(self):
         if self._plan.value is None:
             raise HvoxError(-5, "plan freed")
@@ -350,15 +362,26 @@ class Plan:
             raise ValueError(f"{name} must be on the GPU")
         if x.dtype != self.complex_dtype:
             x = x.to(self.complex_dtype)
-        return x.contiguous(), squeeze
+        # (contiguous() keeps a lazy conjugation or negation, which the raw data pointer does not carry)
+        return x.contiguous().resolve_conj().resolve_neg(), squeeze
 
-    def _out(self, ntrans, n, out):
+    def _out(self, ntrans, n, out, stream):
         torch = _torch()
         if out is None:
             return torch.empty((ntrans, n), dtype=self.complex_dtype, device=self.device)
         if out.shape != (ntrans, n) or out.dtype != self.complex_dtype or not out.is_contiguous():
             raise ValueError("bad output tensor")
+        if out.is_conj() or out.is_neg():   # a lazy view: filled by _deliver
+            with self._on(stream):
+                return torch.empty((ntrans, n), dtype=out.dtype, device=out.device)
         return out
+
+    def _deliver(self, y, out, stream):
+        """The result y of a call given ``out``, copied where out is a lazily conjugated or negated view."""
+        if y is out:
+            return out
+        with self._on(stream):
+            return out.copy_(y)
 
     def _transform(self, fn, x, n_in, n_out, name, out, stream):
         """fn on x: (n_in,) or (ntrans, n_in) to (n_out,) or (ntrans, n_out).  Small calls are bound by this
@@ -366,17 +389,18 @@ class Plan:
         self._check_runnable()
         torch = _torch()
         if isinstance(x, torch.Tensor) and x.is_cuda and x.dtype is self._cdtype and x.is_contiguous() and \
-                x.dim() in (1, 2) and x.shape[-1] == n_in:
+                x.dim() in (1, 2) and x.shape[-1] == n_in and not (x.is_conj() or x.is_neg()):
             squeeze = x.dim() == 1
         else:
-            x, squeeze = self._prep(x, n_in, name)
+            with self._on(stream):
+                x, squeeze = self._prep(x, n_in, name)
         ntrans = 1 if squeeze else x.shape[0]
         if out is None:
             y = torch.empty((n_out,) if squeeze else (ntrans, n_out), dtype=self._cdtype, device=self.device)
         else:
-            y = self._out(ntrans, n_out, out)
+            y = self._out(ntrans, n_out, out, stream)
         _check(fn(self._plan, x.data_ptr(), y.data_ptr(), ntrans, self._stream_handle(stream)))
-        return y
+        return y if out is None else self._deliver(y, out, stream)
 
     def synthesis(self, sky, out=None, stream=None):
         """V[t, k] = sum_n sky[t, n] exp(-2 pi i <p_k, r_n>)."""
@@ -414,29 +438,37 @@ class Plan:
         b: (n_terms, n_pix) complex tensors on the plan's GPU."""
         torch = _torch()
         self._check_runnable()
-        x, squeeze = self._prep(sky, self.n_pix, "sky")
-        ta, tb = self._gains(a, b)
-        y = self._out(x.shape[0], self.n_vis, out)
-        work = torch.empty((2, ta.shape[0], max(self.n_vis, self.n_pix)), dtype=self.complex_dtype, device=self.device)
+        with self._on(stream):
+            x, squeeze = self._prep(sky, self.n_pix, "sky")
+            ta, tb = self._gains(a, b)
+            work = torch.empty((2, ta.shape[0], max(self.n_vis, self.n_pix)), dtype=self.complex_dtype,
+                               device=self.device)
+        y = self._out(x.shape[0], self.n_vis, out, stream)
         _check(self._lib.hvox_synthesis_dde(self._plan, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
                                             ctypes.c_void_p(ta.data_ptr()), ctypes.c_void_p(tb.data_ptr()),
                                             ta.shape[0], x.shape[0], ctypes.c_void_p(work.data_ptr()),
                                             ctypes.c_void_p(self._stream_handle(stream))))
-        return y[0] if squeeze and out is None else y
+        if out is not None:
+            return self._deliver(y, out, stream)
+        return y[0] if squeeze else y
 
     def analysis_dde(self, vis, a, b, out=None, stream=None):
         """The adjoint: I[r, n] = sum_k conj(A_k(r_n)) vis[r, k] exp(+2 pi i <p_k, r_n>)."""
         torch = _torch()
         self._check_runnable()
-        x, squeeze = self._prep(vis, self.n_vis, "vis")
-        ta, tb = self._gains(a, b)
-        y = self._out(x.shape[0], self.n_pix, out)
-        work = torch.empty((2, ta.shape[0], max(self.n_vis, self.n_pix)), dtype=self.complex_dtype, device=self.device)
+        with self._on(stream):
+            x, squeeze = self._prep(vis, self.n_vis, "vis")
+            ta, tb = self._gains(a, b)
+            work = torch.empty((2, ta.shape[0], max(self.n_vis, self.n_pix)), dtype=self.complex_dtype,
+                               device=self.device)
+        y = self._out(x.shape[0], self.n_pix, out, stream)
         _check(self._lib.hvox_analysis_dde(self._plan, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
                                            ctypes.c_void_p(ta.data_ptr()), ctypes.c_void_p(tb.data_ptr()),
                                            ta.shape[0], x.shape[0], ctypes.c_void_p(work.data_ptr()),
                                            ctypes.c_void_p(self._stream_handle(stream))))
-        return y[0] if squeeze and out is None else y
+        if out is not None:
+            return self._deliver(y, out, stream)
+        return y[0] if squeeze else y
 
     def info(self) -> dict:
         inf = HvoxPlanInfo()
