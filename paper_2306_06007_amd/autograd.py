@@ -9,6 +9,17 @@ from __future__ import annotations
 
 import torch
 
+from .hvox import Plan
+
+_PLAN_ANALYSIS = Plan.analysis
+
+
+def _real_adjoint(plan):
+    """The plan's adjoint where only its real part is wanted: a Plan's shorter direct sum, unless
+    a subclass, a wrapper or the object itself brings an analysis of its own, which the gradient follows."""
+    own = getattr(type(plan), "analysis", None) is not _PLAN_ANALYSIS or "analysis" in getattr(plan, "__dict__", {})
+    return plan.analysis if own else plan._analysis_real
+
 
 class HvoxSynthesis(torch.autograd.Function):
     @staticmethod
@@ -22,7 +33,7 @@ class HvoxSynthesis(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g):
         if ctx.real_input:   # only the real part of A^H g is wanted
-            gx = getattr(ctx.plan, "_analysis_real", ctx.plan.analysis)(g.contiguous())
+            gx = _real_adjoint(ctx.plan)(g.contiguous())
             return gx.real.to(ctx.in_dtype), None
         return ctx.plan.analysis(g.contiguous()), None
 
