@@ -56,6 +56,10 @@ constexpr int kDirectTile = 512;     // targets per direct-sum workgroup (two pe
 constexpr int kDirectNarrow = 128;   // the same where wide tiles leave the GPU idle: the wavefronts divide the sources
 constexpr int kDirectSrcTile = 256;  // sources staged in LDS at a time
 constexpr int kDirectSeg = 8192;     // longest source segment of a direct-sum work item
+// float32 items of at most this many sources take sine and cosine in float64: with few terms
+// the error of a term is the error of the sum, and the tile's own reference point, once the phase
+// origin, made the first source exact (one source: 2.8e-8, two 8e-8; by the hardware sine 7e-8 each)
+constexpr int kDirectExactSrc = 2;
 // shorter segments while a plan has fewer direct work items: about ten rounds of the
 // workgroups that the GPU holds (four or five per CU), of which the last is partly
 // empty (138,750 x 150,000 points, float64: 5,149 items in five rounds and a bit, 14.1 ms;

@@ -1241,14 +1241,15 @@ __global__ __launch_bounds__(256) void k_interp(const PairDev *__restrict__ pair
 // <= kDirectSeg sources, staged 256 at a time in LDS, for NT data rows at
 // once (the phase factors are computed once and applied to every row).  Phases
 // are float64 dot products (full rate on CDNA).  Float32 plans take them of the
-// coordinates themselves: a phase of |t| turns is rounded to |t| 2^-53.  Float64
+// coordinates themselves, to 2^-32 turns or |t| 2^-53 for |t| turns (items of one or two
+// sources: in float64 throughout).  Float64
 // plans take them relative to the first source x_S of the staged tile and rotate
 // the tile's sums by exp(2 pi i s_k.x_S), evaluated with exact products.  The
 // sign iota multiplies the target coordinates, so the inner loop always
 // accumulates c exp(+2 pi i t).
 //
 // What bounds it: VALU issue.  Per term the float32 loop issues three float64
-// FMAs (phase), one funnel shift (reduction to a fraction of a turn), sine and
+// FMAs (phase), a conversion and a scaling (fraction of a turn), sine and
 // cosine (two issue cycles each) and the multiply-adds: four, two when every
 // value of the staged tile is real (a real sky) or only the real part of the
 // result is wanted -- 12 or 10 lane-cycles.  Matrix instructions for the
@@ -1270,12 +1271,15 @@ enum DirectMode { kDirectComplex, kDirectRealIn, kDirectRealOut };
 // Float32 phase t + kPhaseMagic, accumulated as such by the FMAs: the sum of
 // 1.5 2^20 keeps every |t| < 2^19 turns (the planner's kMaxMagicTurns bounds them
 // with room) in one binade whose last bit is 2^-32 turns, so the
-// low word of the double is the fraction of a turn in 32 bits.  Its upper 23
-// bits become the mantissa of a float in [1, 2), which the hardware sine and
-// cosine take in revolutions: one funnel shift instead of a float64 fraction
-// and a conversion.  The added 2^-24 centres the truncation to 23 bits (an
-// error of at most 2^-24 turns).
-constexpr double kPhaseMagic = 1572864.0 + 0x1p-24;
+// low word of the double is the fraction of a turn in 32 bits.  Read as a signed
+// integer, converted and scaled it is a float in [-1/2, 1/2] (an error of at most
+// 2^-26 turns, less near zero), which the hardware sine and cosine take in
+// revolutions.  A float64 fraction and its conversion hold a phase no better
+// (2^-25 turns, [0, 1)) and take longer: 3.08e12 against 3.17e12 complex terms/s.
+// One funnel shift of the upper 23 bits into the mantissa of a float in [1, 2) is
+// faster (3.35e12), but its 2^-24 turns at every phase, zero included, are the larger part of a
+// term's error: 3 points seen by 3,000, 2.2e-7 against 7.3e-8 (relative l2).
+constexpr double kPhaseMagic = 1572864.0;
 
 // exp(2 pi i t) of the phase q.x for one (target, source): float32 plans
 template <bool WIDE>
@@ -1287,7 +1291,7 @@ __device__ __forceinline__ void direct_cis(const double q[3], double x, double y
         r = static_cast<float>(__builtin_amdgcn_fract(fma(q[0], x, fma(q[1], y, q[2] * z))));
     } else {
         const double m = fma(q[0], x, fma(q[1], y, fma(q[2], z, kPhaseMagic)));
-        r = __int_as_float(__builtin_amdgcn_alignbit(0x7f, __double2loint(m), 9));   // 1.fraction
+        r = static_cast<float>(__double2loint(m)) * 0x1p-32f;   // [-1/2, 1/2] turns
     }
     s = __builtin_amdgcn_sinf(r);
     c = __builtin_amdgcn_cosf(r);
@@ -1416,7 +1420,23 @@ __device__ __forceinline__ void direct_item(const DirectItem it, const double *_
         const int c4 = (cnt + 3) & ~3, per = (c4 / 4 + SL - 1) / SL * 4;   // this slice's share
         const int jb = SL == 1 ? 0 : min(slice * per, c4), je = SL == 1 ? c4 : min(jb + per, c4);
         if constexpr (!kRef) {
-            if (real_out)
+            // one or two sources: their phases are the whole result, and hold float64
+            if (it.src_cnt <= kDirectExactSrc) {
+                for (int j = jb; j < min(je, cnt); ++j) {
+                    const double x[3] = {lx[j], ly[j], lz[j]};
+                    double c0, s0, c1, s1;
+                    cis_dot(q0, x, c0, s0);
+                    cis_dot(q1, x, c1, s1);
+#pragma unroll
+                    for (int r = 0; r < NT; ++r) {
+                        const double cr = lc[r][j].x, ci = lc[r][j].y;
+                        a0r[r] = fma(cr, c0, fma(-ci, s0, a0r[r]));
+                        a0i[r] = fma(cr, s0, fma(ci, c0, a0i[r]));
+                        a1r[r] = fma(cr, c1, fma(-ci, s1, a1r[r]));
+                        a1i[r] = fma(cr, s1, fma(ci, c1, a1i[r]));
+                    }
+                }
+            } else if (real_out)
                 direct_tile<T, NT, WIDE, kDirectRealOut>(jb, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
             else if (cplx_in)
                 direct_tile<T, NT, WIDE, kDirectComplex>(jb, je, q0, q1, lx, ly, lz, lc, ltab, a0r, a0i, a1r, a1i);
