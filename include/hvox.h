@@ -180,7 +180,7 @@ typedef struct {
 #define HVOX_K_FFT_Z    4
 #define HVOX_K_INTERP   5
 #define HVOX_K_DIRECT   6
-#define HVOX_K_FINAL    7
+#define HVOX_K_FINAL    7   /* sums to the result, and stored direct-sum layers to the accumulator */
 #define HVOX_K_TRANSPOSE 8
 #define HVOX_K_PREPHASE 9   /* gather + pre-phase of the sources of a batch of sub-problems */
 #define HVOX_K_COUNT    10

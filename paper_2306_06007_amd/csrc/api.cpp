@@ -402,7 +402,9 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
             dl.layers = static_cast<int>(group);
             for (int64_t l0 = 0; l0 < dp.layers; l0 += group) {
                 if (l0 > 0) {   // the slabs are needed again: their layers go to the accumulator
-                    HVOX_TRY(launch_add_layers(sc.acc, n_tgt, sc.slab, layer0, dl.layers, dd.tgt_layers, fresh, nb, st));
+                    HVOX_TRY(timed(pl, may_time, HVOX_K_FINAL, st, [&] {
+                        return launch_add_layers(sc.acc, n_tgt, sc.slab, layer0, dl.layers, dd.tgt_layers, fresh, nb, st);
+                    }));
                     fresh = false;
                 }
                 layer0 = dl.layer0 = static_cast<int>(l0);

@@ -65,3 +65,24 @@ def test_direct_sum_keeps_its_order(dtype, n_vis, n_pix):
             for rows in (slice(0, 4), slice(2, 3)):
                 assert torch.equal(_noalloc(p, 0, sky[rows]), V[rows])
                 assert torch.equal(_noalloc(p, 1, vis[rows]), I[rows])
+
+
+def _launches(plan, sky):
+    plan.reset_stats()
+    plan.set_timing(True)
+    plan.synthesis(sky)
+    torch.cuda.synchronize()
+    st = plan.stats()
+    plan.set_timing(False)
+    return st["direct"]["launches"], st["finalize"]["launches"]
+
+
+def test_every_launch_of_the_direct_sum_is_timed():
+    """600,000 targets: the slabs (2^22 values) hold 6 of 10 layers, so the first launch's layers go to the accumulator."""
+    rng = np.random.default_rng(22)
+    uvw, xyz = W.uvw_disk(600_000, 1000.0, 50.0, rng), W.fibonacci_cap(80_000, 5.0)
+    sky = torch.as_tensor(W.complex_normal(4, 80_000, rng)).to("cuda", torch.complex64)
+    with hv.Plan(uvw, xyz, 0.0, "f32", deterministic=True) as p:
+        direct, final = _launches(p, sky[0])
+        assert direct == p.info()["n_direct_layers"] > 1
+        assert final == direct   # all but the last launch's layers by k_add_layers, those by the epilogue
