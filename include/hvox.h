@@ -161,7 +161,8 @@ typedef struct {
                                  for the tile lists, bounded by every source touching 2^3 tiles) */
     int32_t flags;            /* the plan's option flags */
     int32_t on_device;        /* 1 once the device part exists */
-    int64_t n_direct_layers;  /* HVOX_DETERMINISTIC: launches of the direct sum per data-row group */
+    int64_t n_direct_layers;  /* HVOX_DETERMINISTIC: launches of the synthesis' direct sum per group of ntrans_hint
+                                 data rows (more where a call's groups hold more rows: up to one per layer) */
     int64_t noalloc_scratch_bytes;  /* static scratch hvox_transform_noalloc needs for this plan */
     /* occupancy of the NUFFT grids (both directions, device plans): grid-1 tiles (32 x 8 x 8 cells)
      * holding sources, x lines of grid 1 in tile rows holding sources, z planes in tile layers

@@ -317,9 +317,11 @@ int run_direction(hvox_plan_s *pl, bool synthesis, const void *in, void *out, in
         const int nb = static_cast<int>(std::min<int32_t>(kRowBatch, ntrans - t0));
         if (n_tgt == 0) continue;
         // layers of direct items per launch whose sums fit the slabs (0: items add into the accumulator).
-        // Deterministic plans take what fits; others need every layer, or add with atomics
+        // Deterministic plans take what fits, but not one layer of several: stored, it would be
+        // added by a launch of its own; others need every layer, or add with atomics
         const int64_t fit = sc.slab && dp.slab_layers > 0 ? hp.slab_elems / (n_tgt * nb) : 0;
-        const int64_t group = det ? std::min(fit, dp.layers) : (fit >= dp.layers ? dp.layers : 0);
+        const int64_t least = det ? std::min<int64_t>(2, dp.layers) : dp.layers;
+        const int64_t group = fit >= least ? std::min(fit, dp.layers) : 0;
         DirectLaunch dl{dd.direct, 0, dp.direct_tile, sxyz, n_src, txyz, n_tgt, sperm,
                         static_cast<const C *>(in) + static_cast<int64_t>(t0) * n_src, sc.acc, nb, iota, kDirectAtomic,
                         0, 0, hp.wide_phase, real_only, 0, pl->cis_tab, pl->queue};

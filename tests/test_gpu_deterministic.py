@@ -86,3 +86,14 @@ def test_every_launch_of_the_direct_sum_is_timed():
         direct, final = _launches(p, sky[0])
         assert direct == p.info()["n_direct_layers"] > 1
         assert final == direct   # all but the last launch's layers by k_add_layers, those by the epilogue
+
+
+def test_a_single_layer_that_fits_is_added_in_place():
+    """Four rows on a plan made for one: its slabs hold one of 10 layers of four rows, so items add into the accumulator."""
+    rng = np.random.default_rng(22)
+    uvw, xyz = W.uvw_disk(600_000, 1000.0, 50.0, rng), W.fibonacci_cap(80_000, 5.0)
+    sky = torch.as_tensor(W.complex_normal(4, 80_000, rng)).to("cuda", torch.complex64)
+    with hv.Plan(uvw, xyz, 0.0, "f32", deterministic=True) as p:
+        direct, final = _launches(p, sky)
+        assert direct == 10 and final == 1
+        assert torch.equal(p.synthesis(sky)[2], p.synthesis(sky[2]))
