@@ -17,7 +17,11 @@ the FP64 oracle on a bounded sample of output rows, extrapolated linearly.
 ``--workload dense-10km`` reports the same line for the dense 30-degree DCOS
 mesh of the 10 km telescope radius (238,203 vis x 10,240,000 pix) instead.
 
-Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu-baseline]
+The printed line holds the step and a digest of the runs beside it, in less
+than RESULT_LINE_MAX characters; ``--report FILE`` writes everything measured
+(per-kernel tables, rooflines of every mode, each served request's error).
+
+Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu-baseline] [--report FILE]
 """
 from __future__ import annotations
 
@@ -191,6 +195,54 @@ VALU_CYCLES_PER_TERM = {("f32", 1): 81 / 8, ("f32", 2): 97 / 16, ("f32", 3): 113
                         ("f64", 1): 170 / 8, ("f64", 2): 202 / 16, ("f64", 3): 234 / 24, ("f64", 4): 266 / 32}
 
 
+# readers of the result keep the last few thousand characters of the output
+RESULT_LINE_MAX = 4000
+
+
+def _brief(v):
+    """v with its floats at five significant digits (the step's own value and time are printed in full)."""
+    if isinstance(v, float):
+        return float(f"{v:.5g}")
+    if isinstance(v, dict):
+        return {k: _brief(x) for k, x in v.items()}
+    return v
+
+
+def result_line(out) -> str:
+    """The JSON line printed for a report: the fields of the step as they are, and of the rest what
+    fits RESULT_LINE_MAX (per mode its time and errors, of the served requests the summary)."""
+    head = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config")
+    line = {k: out[k] for k in head}
+    line["roofline_kernel"] = out["roofline_kernel"]
+    line["roofline"] = _brief(out["roofline"])
+    extra = {}
+    if out.get("f64"):
+        extra["f64"] = _brief({**out["f64"], "roofline": {k: out["f64"]["roofline"][k]
+                                                          for k in ("bound", "achieved", "peak", "unit", "frac")}})
+    for k in ("f32_over_f64", "plan_seconds", "rel_l2_vs_oracle", "cpu_baseline"):
+        if out.get(k) is not None:
+            extra[k] = _brief(out[k])
+    if out.get("directions"):
+        extra["directions_median_ms"] = {d: {k[:-3]: _brief(v["median"]) for k, v in t.items() if isinstance(v, dict)}
+                                         for d, t in out["directions"].items()}
+    if out.get("serving"):
+        s = out["serving"]
+        extra["serving"] = _brief({k: v for k, v in s.items() if not isinstance(v, (dict, list))})
+        if "vs_oracle" in s:
+            extra["serving"]["rel_l2_max"] = _brief(s["vs_oracle"]["rel_l2_max"])
+            extra["serving"]["all_within_eps"] = s["vs_oracle"]["all_within_eps"]
+    if out.get("modes"):
+        extra["modes_ms_per_step"] = {m: _brief(r["ms_per_step"]) for m, r in out["modes"].items()}
+        extra["modes_rel_l2_max"] = {m: _brief(max(r["rel_l2_vs_oracle"]["synthesis"], r["rel_l2_vs_oracle"]["analysis"]))
+                                     for m, r in out["modes"].items() if "rel_l2_vs_oracle" in r}
+    extra["source_hash"] = out["source_hash"]
+    for k, v in extra.items():   # in this order while there is room
+        if len(json.dumps({**line, k: v})) < RESULT_LINE_MAX:
+            line[k] = v
+    return json.dumps(line)
+
+
 def host_cpu_model() -> str:
     """The host processor's model name (Linux /proc/cpuinfo), or "unknown"."""
     try:
@@ -326,6 +378,7 @@ def main():
     ap.add_argument("--dist-runs", type=int, default=20,
                     help="passes of synthesis then analysis timed one by one with HIP events for the per-direction "
                          "median / p10 / p90 of the float32 and float64 plans (0: skip)")
+    ap.add_argument("--report", default="", metavar="FILE", help="also write everything measured to FILE (JSON)")
     ap.add_argument("--copy-probe", type=int, default=0, metavar="MIB",
                     help="only run a plain device copy of MIB mebibytes three times (counter calibration)")
     args = ap.parse_args()
@@ -591,7 +644,10 @@ def main():
         if "serving" in out:
             log("serving results against the oracle (1,024 sampled rows per request)...")
             out["serving"]["vs_oracle"] = serving_errors(serving_reqs, serving_res)
-    print(json.dumps(out), flush=True)
+    if args.report:
+        with open(args.report, "w") as fh:
+            json.dump(out, fh)
+    print(result_line(out), flush=True)
 
 
 if __name__ == "__main__":
