@@ -43,9 +43,10 @@ def test_row_alone_and_among_others(dtype, n_vis, n_pix):
 
 
 # (2,000, 3,072): some 24 layers in the plan's slabs and the static buffer; (200,000, 160,000): 20 layers of 200,000
-# targets, which the plan's slabs hold (2^22 values) and the 64 MiB static buffer does not
+# targets, which the plan's slabs hold (2^22 values) and the 64 MiB static buffer does not; (3, 60,000) and (500, 40,001):
+# hundreds of layers of few targets, whose loads several lanes share
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
-@pytest.mark.parametrize("n_vis,n_pix", [(2_000, 3_072), (200_000, 160_000)])
+@pytest.mark.parametrize("n_vis,n_pix", [(2_000, 3_072), (200_000, 160_000), (3, 60_000), (500, 40_001)])
 def test_direct_sum_keeps_its_order(dtype, n_vis, n_pix):
     cd = torch.complex64 if dtype == "f32" else torch.complex128
     rng = np.random.default_rng(21)
