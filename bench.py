@@ -132,13 +132,16 @@ def kernel_table(plan, bufs):
     return st
 
 
+# every workload's step is a synthesis of a real sky and an analysis of complex visibilities over about as many terms
+REAL_SHARE = 0.5
 HBM_KERNELS = ("zero", "spread", "fft_x", "fft_y", "fft_z", "interp", "finalize", "transpose", "prephase")
 
 
-def roofline_entry(st, dtype, name=None, rows=1, mode="auto"):
+def roofline_entry(st, dtype, name=None, rows=1, mode="auto", real_share=0.0):
     """Roofline of one kernel (default: the one taking the most time): its
     algorithmic bytes (or arithmetic) per launch over its average launch
-    duration, against the MI355X peak."""
+    duration, against the MI355X peak.  real_share: the part of the direct sum's
+    terms with real source values."""
     hbm_kernels = HBM_KERNELS
     if name is None:
         name = max(st, key=lambda k: st[k]["ms"])
@@ -159,13 +162,14 @@ def roofline_entry(st, dtype, name=None, rows=1, mode="auto"):
     terms_per_s = v["alg_flops"] / n / avg_s if avg_s > 0 else 0.0
     achieved = terms_per_s * ALG_OPS_PER_TERM / 1e12
     peak = VECTOR_PEAK_TFLOPS[dtype]
-    bound = LANE_CYCLES_PER_S / VALU_CYCLES_PER_TERM[(dtype, rows)]
+    mix = lambda c, r: real_share * r[(dtype, rows)] + (1.0 - real_share) * c[(dtype, rows)]  # noqa: E731
+    bound = LANE_CYCLES_PER_S / mix(VALU_CYCLES_PER_TERM, VALU_CYCLES_PER_TERM_REAL)
     return name, {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                   "frac": achieved / peak, "traffic": measured_traffic(name, dtype, mode),
                   "ops_per_term": ALG_OPS_PER_TERM,
                   "issue_bound": {"term_rows_per_s": bound, "achieved_term_rows_per_s": terms_per_s,
                                   "frac": terms_per_s / bound,
-                                  "valu_instr_per_term_row": VALU_OPS_PER_TERM[(dtype, rows)]}}
+                                  "valu_instr_per_term_row": mix(VALU_OPS_PER_TERM, VALU_OPS_PER_TERM_REAL)}}
 
 
 # Algorithmic operations of one direct-sum term (target k, source n), the count
@@ -174,25 +178,28 @@ def roofline_entry(st, dtype, name=None, rows=1, mode="auto"):
 # complex multiply-accumulate (8): about 30 operations per term.
 ALG_OPS_PER_TERM = 30.0
 # VALU instructions issued per (target, source, data row) by the direct
-# kernel's inner loop, counted from its gfx950 assembly (the loop that reads
-# the staged sources from LDS, complex source values, 512-target tiles; LDS
-# reads and scalar loop control excluded), by plan precision and rows per
-# launch.  Per iteration of 4 sources x 2 targets: float32, the float64 dot
-# product that leaves the fraction of a turn in its low word, its extraction and
-# hardware sine and cosine (shared by the rows); float64, the dot product, the
-# 1024-entry phase table's index and remainder, the remainder's Taylor sine and
-# cosine and the rotation by the table entry (shared); then one complex
-# multiply-accumulate per row.  Each is one lane-operation per lane.  Tiles whose
-# source values are all real (a sky of intensities) issue two instructions less
-# per term-row, so such a synthesis can pass the complex loop's bound.
-VALU_OPS_PER_TERM = {("f32", 1): 81 / 8, ("f32", 2): 113 / 16, ("f32", 3): 145 / 24, ("f32", 4): 177 / 32,
-                     ("f64", 1): 170 / 8, ("f64", 2): 202 / 16, ("f64", 3): 234 / 24, ("f64", 4): 266 / 32}
-# Lane-cycles per term-row of the same loops at the per-class issue rates
-# (float32 arithmetic 1/2 cycle, hardware sine / cosine 2, the rest 1): float32
-# 32 / 64 / 96 / 128 float32 + 16 transcendental + 33 other per 8 / 16 / 24 / 32
-# term-rows; float64 has no float32 or transcendental instructions.
-VALU_CYCLES_PER_TERM = {("f32", 1): 81 / 8, ("f32", 2): 97 / 16, ("f32", 3): 113 / 24, ("f32", 4): 129 / 32,
-                        ("f64", 1): 170 / 8, ("f64", 2): 202 / 16, ("f64", 3): 234 / 24, ("f64", 4): 266 / 32}
+# kernel's inner loops, counted from their gfx950 assembly (the loops that read
+# the staged sources from LDS, 512-target tiles; LDS reads and scalar loop control
+# excluded), by plan precision and rows per launch.  Per iteration of 4 sources x 2
+# targets: float32, the float64 dot product that leaves the fraction of a turn in its
+# low word, its conversion and scaling, and hardware sine and cosine (shared by the
+# rows); float64, the dot product, the 1024-entry phase table's index and remainder,
+# the remainder's Taylor sine and cosine and the rotation by the table entry (shared);
+# then per row one complex multiply-accumulate, or half of it (VALU_*_REAL) where every
+# staged value is real, as a sky of intensities, or only the real part of the result is
+# wanted.  Each is one lane-operation per lane.
+VALU_OPS_PER_TERM = {(t, r): (s + 32 * r) / (8 * r) for t, s in (("f32", 57), ("f64", 138)) for r in (1, 2, 3, 4)}
+VALU_OPS_PER_TERM_REAL = {(t, r): (s + 16 * r) / (8 * r) for t, s in (("f32", 57), ("f64", 138)) for r in (1, 2, 3, 4)}
+# Lane-cycles per term-row of the same loops at the per-class peak issue rates
+# (float32 arithmetic 1/2 cycle, hardware sine / cosine 2, the rest 1): float32, per
+# iteration, 16 transcendental, 33 other and 8 + 32 (8 + 16 real) float32
+# per row; float64 has no float32 or transcendental instructions.  Peak rates: measured in a loop
+# on registers alone, float32 multiply-adds take 0.7 to 0.85, so the single-row float32
+# loops reach 86% (complex) and 90% (real) of this bound with nothing left to hide.
+VALU_CYCLES_PER_TERM = {("f32", r): (69 + 16 * r) / (8 * r) for r in (1, 2, 3, 4)}
+VALU_CYCLES_PER_TERM.update({("f64", r): VALU_OPS_PER_TERM["f64", r] for r in (1, 2, 3, 4)})
+VALU_CYCLES_PER_TERM_REAL = {("f32", r): (69 + 8 * r) / (8 * r) for r in (1, 2, 3, 4)}
+VALU_CYCLES_PER_TERM_REAL.update({("f64", r): VALU_OPS_PER_TERM_REAL["f64", r] for r in (1, 2, 3, 4)})
 
 
 # readers of the result keep the last few thousand characters of the output
@@ -524,7 +531,7 @@ def main():
         head_mode = "threshold"          # no counter summaries are taken at other thresholds
     elif args.direct_threshold == 0:
         head_mode = "dense_10km_forced_nufft" if dense_head else "forced_nufft"
-    kname, roof = roofline_entry(r32["stats"], "f32", mode=head_mode)
+    kname, roof = roofline_entry(r32["stats"], "f32", mode=head_mode, real_share=REAL_SHARE)
     out = {
         "metric": METRIC,
         "value": value,
@@ -546,7 +553,7 @@ def main():
         "roofline": roof,
         "roofline_kernel": kname,
         "f64": ({"value": n_units / r64["sec"], "ms_per_step": r64["sec"] * 1e3, "steps": r64["steps"], "eps": 1e-9,
-                 "roofline": roofline_entry(r64["stats"], "f64", mode=head_mode)[1],
+                 "roofline": roofline_entry(r64["stats"], "f64", mode=head_mode, real_share=REAL_SHARE)[1],
                  "roofline_kernel": roofline_entry(r64["stats"], "f64", mode=head_mode)[0]}
                 if r64 else None),
         "f32_over_f64": r64["sec"] / r32["sec"] if r64 else None,
@@ -586,7 +593,7 @@ def main():
             roofs = {}
             for k, v in r["stats"].items():
                 if v["launches"] and v["ms"] > 0 and (v["alg_bytes"] or k == "direct"):
-                    _, rf = roofline_entry(r["stats"], r["dtype"], k, rows=rows, mode=m)
+                    _, rf = roofline_entry(r["stats"], r["dtype"], k, rows=rows, mode=m, real_share=REAL_SHARE)
                     roofs[k] = {"bound": rf["bound"], "achieved": round(rf["achieved"], 1), "unit": rf["unit"],
                                 "frac": round(rf["frac"], 4)}
                     if "issue_bound" in rf:

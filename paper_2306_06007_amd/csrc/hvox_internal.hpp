@@ -261,7 +261,7 @@ struct DirPlan {                         // one direction (synthesis or analysis
     int direct_tile = kDirectTile;           // targets per item (kDirectTile or kDirectNarrow)
     // layers whose items may run in one launch, each storing its sums in a slab of its own that
     // is added up afterwards, layer after layer (0: items add into the accumulator), the layers in
-    // all, and those of every target (chunk order, device copy released after the upload)
+    // all, and those of every target (chunk order; the epilogue reads a device copy)
     int64_t slab_layers = 0, layers = 0;
     std::vector<int32_t> tgt_layers;
     double grid_cells = 0.0, direct_terms = 0.0;

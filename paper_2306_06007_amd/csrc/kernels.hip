@@ -747,8 +747,8 @@ __global__ __launch_bounds__(NT) void k_fft_pass(const PairDev *__restrict__ pai
 // pass y reads four neighbouring lines as one contiguous run.  No transpose.
 //
 // What bounds it: load, transform, exchange and store of a line follow each other,
-// and LDS and registers let only two to three wavefronts per SIMD overlap
-// them: leaving out loads, stores, transforms or twiddles each saved about a fifth.
+// and registers let only three (float32, 168) or two wavefronts per SIMD (float64, 228)
+// overlap them: leaving out loads, stores, transforms or twiddles each saved about a fifth.
 // VALU is busy 45% of the time, traffic is 2.1 (x) and 3.3 TB/s (y, float32), 2.7 and 4.2
 // TB/s (float64) of 4.7 for a copy.  Of the general passes it replaces (four or five radix
 // stages of a 1200-point line, each with its index arithmetic, an LDS round
@@ -756,7 +756,9 @@ __global__ __launch_bounds__(NT) void k_fft_pass(const PairDev *__restrict__ pai
 // the 3 km dense mesh with every sub-problem a NUFFT (float32; now 15.5) and 11.0 ms on
 // the 1 km one (float64; now 5.8).  Tried: several groups of lines per workgroup
 // (8% slower), twiddles staged in LDS (4% slower: another barrier), smaller
-// groups (10% slower), 128 registers (spills; lengths up to 27 x 27 only).  Longer
+// groups (10% slower), 128 registers (more spills; lengths up to 27 x 27 only).  One
+// instance serves every factor: the 36- and 40-point transforms spill 40 (x) and 48 bytes (y)
+// a lane in float32, and short lines run at the longest factor's registers.  Longer
 // factors than 27 in float64 would take more than 256 registers.
 // ---------------------------------------------------------------------------
 
@@ -1248,21 +1250,23 @@ __global__ __launch_bounds__(256) void k_interp(const PairDev *__restrict__ pair
 // sign iota multiplies the target coordinates, so the inner loop always
 // accumulates c exp(+2 pi i t).
 //
-// What bounds it: VALU issue.  Per term the float32 loop issues three float64
-// FMAs (phase), a conversion and a scaling (fraction of a turn), sine and
-// cosine (two issue cycles each) and the multiply-adds: four, two when every
-// value of the staged tile is real (a real sky) or only the real part of the
-// result is wanted -- 12 or 10 lane-cycles.  Matrix instructions for the
+// What bounds it: VALU issue.  Per (target, source) the float32 loop issues three
+// float64 FMAs (phase), a conversion and a scaling (fraction of a turn), sine and
+// cosine, and per row four multiply-adds, two when every value of the staged tile is
+// real (a real sky) or only the real part of the result is wanted: 11.1 instructions
+// with one complex row, 9.1 with a real one.  Sine and cosine take two lane-cycles each
+// and do not overlap with the rest; float32 multiply-adds on vector registers take 0.7 to
+// 0.85.  A loop of the same instructions on registers alone takes 12.4 / 10.5 lane-cycles
+// of the 2.4 GHz peak clock (five wavefronts per SIMD; four rows, at three, 23.1 / 15.9),
+// and this one 12.4 / 10.6 (22.5 / 16.1): staging and LDS reads are hidden.  Matrix instructions for the
 // multiply-adds (v_mfma_f32_4x4x1) do not overlap with the vector work and
 // measured 15.1 lane-cycles a term against 12.0.  The float64 loop issues 21.25
-// instructions (19.25 with real values) but takes 25.5 (23.0) lane-cycles of the
-// 2.4 GHz peak clock; without its table reads it measured 21.2 for 18
-// instructions, so the rest is not LDS (a clock held down by float64 power
-// fits).  247,500 x 250,000, 10^12 term-rows/s, real / complex values, before
-// (references per target and source tile, fraction and conversion, one path for
+// instructions (19.25 with real values), which take 22.5 (20.3) lane-cycles on registers
+// alone, and takes 25.2 (22.9).  247,500 x 250,000, 10^12 term-rows/s, real / complex values, before
+// (references per target and source tile, float64 fraction, one path for
 // both kinds of values) and now:
-//   float32, 1 row 3.00 -> 3.92 / 3.34, 4 rows 7.16 -> 10.2 / 7.20;
-//   float64, 1 row 1.50 -> 1.71 / 1.54, 4 rows 3.64 -> 4.84 / 3.72.
+//   float32, 1 row 3.00 -> 3.70 / 3.18, 4 rows 7.16 -> 9.8 / 7.0;
+//   float64, 1 row 1.50 -> 1.71 / 1.56, 4 rows 3.64 -> 4.9 / 3.8.
 // ---------------------------------------------------------------------------
 
 // multiply-adds of a term: complex, real values only, real part of the result only

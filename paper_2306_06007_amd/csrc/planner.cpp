@@ -33,13 +33,13 @@ constexpr double kPi = 3.14159265358979323846;
 // in float32 and ~8e11 in float64 (its 14-wide footprints fill more lanes of
 // a wavefront, and float64 FMAs issue at the float32 rate); the direct
 // kernel 3.0e12 (float32) and 1.35e12 (float64) terms/s.  The kernels have
-// become faster than that (float32 direct sum 3.3e12 to 3.9e12, grid passes
-// without the transpose), the grids by more: with the decision threshold at 0.7
-// / 1 / 1.2 / 1.5 / 2 the SKA-like float32 synthesis takes 215 / 188 / 181 / 178 /
-// 195 ms, its analysis 253 / 221 / 212 / 210 / 215 ms, the 3 km dense mesh 8.5 / 8.5 /
-// 8.6 / 8.5 / 8.8 ms.  The rates stay: a higher threshold moves terms from the direct
+// become faster than that (float32 direct sum 3.2e12 to 3.7e12, two-factor batches
+// without the transpose that the byte model still counts), the grids by more: with the
+// decision threshold at 0.7 / 1 / 1.2 / 1.5 / 2 the SKA-like float32 synthesis takes 227 / 198 /
+// 190 / 189 / 204 ms, its analysis 267 / 236 / 223 / 219 / 222 ms, the 3 km dense mesh 8.7 to
+// 9.0 ms at each.  The rates stay: a higher threshold moves terms from the direct
 // sum (errors of 1e-7) to grids (errors of the order of eps), and what a plan
-// delivers should not lose accuracy for those 4 to 6%.  Callers choose
+// delivers should not lose accuracy for those 4 to 7%.  Callers choose
 // direct_threshold themselves where they prefer the time.
 struct Rates {
     double hbm_bytes_per_s;     // effective streaming rate of the grid passes
@@ -563,9 +563,11 @@ double pair_direct_seconds(int64_t ns, int64_t nt, int dtype)
 
 // Cost of `rows` data rows relative to one: the direct kernel evaluates each
 // phase factor once for up to kRowBatch rows, so every further row of a group
-// adds only its multiply-adds (2 of the 10 to 11 issue cycles of a float32
-// term and 4 of the 21 to 22 of a float64 term, from the direct kernel's
-// inner-loop instruction counts); a NUFFT sub-problem repeats every stage per row.
+// adds only its multiply-adds, 0.18 of a term here.  Measured, a row of real values adds 0.17
+// (float32) or 0.13 (float64), a complex one 0.27 or 0.21; the plan serves both
+// directions, and a higher factor would move sub-problems of multi-row plans from the
+// direct sum to grids, with the errors of the order of eps that brings.  A NUFFT
+// sub-problem repeats every stage per row.
 double direct_rows_factor(int rows, int dtype)
 {
     const double extra = dtype == HVOX_F64 ? 4.0 / 22.25 : 2.0 / 11.125;
