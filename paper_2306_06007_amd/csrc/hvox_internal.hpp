@@ -76,8 +76,8 @@ constexpr int kDirectNarrowSeg = 128;
 constexpr int64_t kSlabElems = int64_t(1) << 20, kSlabElemsDet = int64_t(1) << 22;
 // Direct-sum workgroups per CU while NUFFT work runs beside it: a persistent grid fed from a
 // queue, which leaves the two-factor FFT passes the registers they need.  Swept (1 / 2 / 3 / 4 /
-// one workgroup per item, ms): 995,000 x 1M points, float32, synthesis 198 / 184 / 200 / 210 / 211,
-// analysis 232 / 221 / 227 / 233 / 234; 3 km dense mesh 9.1 / 8.7 / 8.8 / 9.0 / 9.0.
+// one workgroup per item, ms): 995,000 x 1M points, float32, synthesis 206 / 197 / 208 / 217 / 217,
+// analysis 244 / 235 / 238 / 243 / 244; 3 km dense mesh 8.9 / 8.6 / 8.9 / 9.1 / 9.1.
 constexpr int kDirectWgPerCu = 2;
 constexpr int kDirectHelpPerCu = 4;  // and those that join them once the NUFFT work is done
 // float32 direct sum: phases of at most this many turns take their fraction from the
