@@ -48,3 +48,19 @@ def test_few_sources(direction, n_src):
     the hardware sine.  A fraction cut to 2^-24 turns is off by 2.2e-7 rad by itself."""
     out, ref, _ = _run(direction, n_src, 3000, 1, 1.0)
     assert np.linalg.norm(out - ref) <= 2.0 ** -23 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e3])
+def test_many_positive_intensities(scale):
+    """A million positive intensities add up what sine and cosine average over a turn: 5e-10 a term would be 4e-7 of
+    the result.  Without it the independent errors of the terms and of the runs remain, 2^-22 at most."""
+    rng = np.random.default_rng(43)
+    uvw, xyz = W.ska_like_uvw(7), W.fibonacci_cap(1_000_000, 10.0)
+    # baselines that resolve the cap; beyond 2^18 turns: the float64 fraction
+    uvw = scale * rng.permutation(uvw[np.linalg.norm(uvw, axis=1) > 500.0])[:256]
+    sky = rng.random((1, 1_000_000)).astype(np.float32).astype(np.complex128)
+    with hv.Plan(uvw, xyz, 0.0, "f32") as p:
+        out = p.synthesis(torch.as_tensor(sky).to("cuda", torch.complex64)).cpu().numpy()
+    ref = oracle.synthesis(uvw, xyz, sky)
+    print(np.linalg.norm(out - ref) / np.linalg.norm(ref), flush=True)
+    assert np.linalg.norm(out - ref) <= 2.0 ** -22 * np.linalg.norm(ref)
